@@ -310,7 +310,7 @@ bool graph_iter_ok(const Mat &X) {
         if (table_lookup(b, b, b, &tp) && tp.family != 3) return false;
         int gr = 2, gc = 2;
         quad_shape(b, &gr, &gc);
-        return gr == 2 && gc == 2;
+        return gr == gc;
     }
     // mixed sizes: the paired groups in one persistent launch per multiply
     return in_mixed_set(X.h_rbs) && smm_variant() == kSmmF64MQuad;

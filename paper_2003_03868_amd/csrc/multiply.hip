@@ -73,13 +73,16 @@ static bool lowp_quad(int prec) {
 }
 
 // k segments of the group lists' symbolic walk (one workgroup per row group
-// and segment, so the serial walk over the merged A rows is nseg times
-// shorter): one per 256 block columns of A, at most 8; BSM_QUAD_KSEG
-// overrides it (tests force several segments on small matrices).
+// and segment; the walk over the merged A rows is serial, so it is nseg times
+// shorter).  One per 4 block columns of A, at most 16, above 1024 block
+// columns at most 8.  Whole multiplies of size 23, 1 / 4 / 8 / 16 / 32
+// segments: 64 block rows 0.55 / 0.45 / 0.43 / 0.41 / 0.41 ms; 300: 2.71 /
+// 2.23 / 2.12 / 2.06 / 2.14; 800 (11% filled): 6.35 / 6.03 / 5.91 / 5.98 /
+// 6.06; 2048 (4.5%): 15.16 / 15.18 / 14.98 / 15.09 / 15.51 (every segment
+// marks the row group's columns again).  BSM_QUAD_KSEG overrides it.
 int32_t quad_ksegments(int32_t nbk) {
     const char *e = getenv("BSM_QUAD_KSEG");
-    int32_t v = e ? atoi(e) : nbk / 256;
-    if (v > 8 && !e) v = 8;
+    int32_t v = e ? atoi(e) : std::min(nbk / 4, nbk > 1024 ? 8 : 16);
     if (v > 64) v = 64;
     return v < 1 ? 1 : v;
 }

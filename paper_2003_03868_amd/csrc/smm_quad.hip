@@ -401,9 +401,13 @@ bool smm_quad_available(int m, int n, int k) {
     return m == n && n == k && (m == 5 || m == 6 || m == 13 || m == 23 || m == 26 || m == 32);
 }
 
+// Size 23 has the 4 x 4 kernel of smm_tile.hip, whose block products took less
+// time than the quads' at every size measured: 395 -> 314 ms on the square of
+// a settled iterate (2048 block rows, 25% filled), 15.3 -> 13.9 ms at 4.5%,
+// 2.03 -> 1.62 ms at 300 block rows (30%), 0.092 -> 0.082 ms at 64 (50%).
 void quad_shape(int m, int *gr, int *gc) {
     const char *e = getenv("BSM_QUAD_GROUP");
-    const int g = e ? atoi(e) : 2;
+    const int g = e ? atoi(e) : (m == 23 ? 4 : 2);
     *gr = *gc = 2;
     if (m == 5 || m == 6) return;
     if (g == 4) { *gr = 4; *gc = 4; }
@@ -441,10 +445,10 @@ int launch_quad(const SmmArgs &a, hipStream_t s) {
         BSM_HIP(hipGetLastError());
         return BSM_OK;
     }
+    if (a.q_gr == 4 && a.q_gc == 4 && a.uni_m == 23) return launch_tile(a, g, s);
     if (a.q_gr == 4 && a.q_gc == 4) {
         switch (a.uni_m) {
             case 13: BSM_LAUNCH((k_smm_f64_quad<13, 4, 4, 16, 8, 1>), g, 1024, 0, s)(a); break;
-            case 23: BSM_LAUNCH((k_smm_f64_quad<23, 4, 4, 16, 8, 1>), g, 1024, 0, s)(a); break;
             case 26: BSM_LAUNCH((k_smm_f64_quad<26, 4, 4, 16, 4, 1>), g, 1024, 0, s)(a); break;
             case 32: BSM_LAUNCH((k_smm_f64_quad<32, 4, 4, 16, 4, 1>), g, 1024, 0, s)(a); break;
             default: set_error("no group-of-sixteen kernel for block size %d", a.uni_m); return BSM_EINVAL;
