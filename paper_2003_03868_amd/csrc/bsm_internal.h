@@ -108,8 +108,10 @@ struct MulSizes {
     int64_t nnzb = 0;        // C blocks after the filter
     int64_t nval_u = 0;      // C scalars before the filter
     int64_t nval = 0;        // C scalars after the filter
+    int64_t n_products = 0;  // block products
     int64_t n_groups = 0;    // groups of C blocks of the group kernel, over all chunks
     int64_t n_entries = 0;   // their entries
+    int gr = 0;              // rows of a group (0: as in the graphs that counted them)
     bool groups = false;     // an FP64 group kernel did the products (uniform sizes, or
                              // mixed sizes in one launch)
 };

@@ -309,7 +309,7 @@ bool graph_iter_ok(const Mat &X) {
         SmmParams tp;
         if (table_lookup(b, b, b, &tp) && tp.family != 3) return false;
         int gr = 2, gc = 2;
-        quad_shape(b, &gr, &gc);
+        quad_shape(b, 0.0, &gr, &gc);
         return gr == gc;
     }
     // mixed sizes: the paired groups in one persistent launch per multiply
@@ -577,7 +577,8 @@ int gi_enter(GraphIter *g, Mat &X, Mat &Y, const MulSizes &sq, const MulSizes &u
             mixed_pairs(X.h_rbs, X.h_cbs, &g->mp);
             g->nrg = g->mp.band_g0.back();
         } else {
-            quad_shape(g->b, &g->gr, &g->gc);
+            quad_shape(g->b, sq.nnzb_u ? static_cast<double>(sq.n_products) / static_cast<double>(sq.nnzb_u) : 0.0,
+                       &g->gr, &g->gc);
             g->nrg = (static_cast<int64_t>(g->nbr) + g->gr - 1) / g->gr;
         }
         g->nseg = quad_ksegments(X.nbcols);
@@ -603,8 +604,10 @@ int gi_enter(GraphIter *g, Mat &X, Mat &Y, const MulSizes &sq, const MulSizes &u
     Caps want;
     want.c = grow(std::max(sq.nnzb_u, up.nnzb_u), dense, m[0]);
     want.cv = grow(std::max(sq.nval_u, up.nval_u), dense_v, m[0]);
-    want.g = grow(std::max(sq.n_groups, up.n_groups), g->nrg * ncg, m[1]);
-    want.e = grow(std::max(sq.n_entries, up.n_entries), INT32_MAX, m[2]);
+    // a 4 x 4 group (entry) is up to four 2 x 2 ones
+    auto own = [&](const MulSizes &z, int64_t v) { return z.gr > g->gr ? 4 * v : v; };
+    want.g = grow(std::max(own(sq, sq.n_groups), own(up, up.n_groups)), g->nrg * ncg, m[1]);
+    want.e = grow(std::max(own(sq, sq.n_entries), own(up, up.n_entries)), INT32_MAX, m[2]);
     want.x = std::max(X.nnzb, grow(std::max(up.nnzb, X.nnzb), dense, m[3]));
     want.xv = std::max(X.nvalues, grow(std::max(up.nval, X.nvalues), dense_v, m[3]));
     want.y = grow(sq.nnzb, dense, m[4]);

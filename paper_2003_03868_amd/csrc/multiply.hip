@@ -295,14 +295,29 @@ int multiply(double alpha, Mat &A, Mat &B, double beta, Mat &C, double eps, int 
     }
     // the quad kernel serves uniform sizes with a compile-time shape unless
     // the tuning table picks another kernel family for them
+    const double reuse = nnzb_c ? static_cast<double>(nprod) / static_cast<double>(nnzb_c) : 0.0;
     bool use_quad = false;
     if (prec == BSM_FP64 && variant == kSmmF64Quad && A.uni_r && A.uni_c && B.uni_c &&
         smm_quad_available(A.uni_r, B.uni_c, A.uni_c)) {
         SmmParams tp;
         use_quad = !(table_lookup(A.uni_r, B.uni_c, A.uni_c, &tp) && tp.family != 3);
-        if (use_quad && tau == 0.0 && !getenv("BSM_SMM_VARIANT") &&
-            static_cast<double>(nprod) < quad_min_reuse() * static_cast<double>(nnzb_c))
+        if (use_quad && tau == 0.0 && !getenv("BSM_SMM_VARIANT") && reuse < quad_min_reuse())
             use_quad = false;
+    }
+    // the other uniform sizes: 4 x 4 groups instead of the run-time-shape
+    // kernel where the table has no choice for the size, C blocks have enough
+    // products, and the time saved exceeds the 0.1 ms that building the groups
+    // adds to a small multiply.  Products per C block, products, whole multiply
+    // with the run-time-shape kernel and with groups: size 9 11.6, 1.9e5, 0.30
+    // and 0.34 ms; 14.7, 2.1e6, 9.5 and 5.7; 172, 1.8e8, 90 and 29; size 17
+    // 11.6, 1.9e5, 0.43 and 0.40; 172, 1.8e8, 196 and 83; size 31 11.6, 1.9e5,
+    // 0.93 and 0.75; 172, 1.8e8, 617 and 251; size 4 11.6, 1.9e5, 0.25 and 0.30;
+    // 172, 1.8e8, 40 and 13.
+    if (prec == BSM_FP64 && variant == kSmmF64Quad && tau == 0.0 && A.uni_r && A.uni_r == A.uni_c &&
+        A.uni_r == B.uni_c && !smm_quad_available(A.uni_r, A.uni_r, A.uni_r) && smm_tile_available(A.uni_r)) {
+        SmmParams tp;
+        use_quad = !table_lookup(A.uni_r, A.uni_r, A.uni_r, &tp) && reuse >= quad_min_reuse() &&
+                   static_cast<double>(nprod) * A.uni_r >= 5e5 * quad_min_reuse();
     }
     // reduced precision: quads where they pay, unless another kernel
     // variant is asked for
@@ -312,7 +327,7 @@ int multiply(double alpha, Mat &A, Mat &B, double beta, Mat &C, double eps, int 
     // group shape: quads, or other shapes on request (FP64 only); screening
     // runs through the quads' product masks
     int GR = 2, GC = 2;
-    if (use_quad && prec == BSM_FP64 && tau == 0.0) quad_shape(A.uni_r, &GR, &GC);
+    if (use_quad && prec == BSM_FP64 && tau == 0.0) quad_shape(A.uni_r, reuse, &GR, &GC);
     if (st == BSM_OK && tau > 0.0 && !use_quad) {
         set_error("product screening needs uniform block sizes 5, 6, 13, 23, 26 or 32 and the "
                   "default kernel variant");
@@ -673,8 +688,10 @@ int multiply(double alpha, Mat &A, Mat &B, double beta, Mat &C, double eps, int 
         sizes->nnzb = nnzb_after;
         sizes->nval_u = nval_c;
         sizes->nval = nc.nvalues;
+        sizes->n_products = nprod;
         sizes->n_groups = sum_groups;
         sizes->n_entries = sum_entries;
+        sizes->gr = GR;
         sizes->groups = (use_quad && prec == BSM_FP64) || use_mquad;
     }
     if (stats) {

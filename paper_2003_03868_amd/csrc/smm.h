@@ -97,12 +97,13 @@ int smm_bench(int m, int n, int k, int64_t n_c, int per_c, int n_prm, const SmmP
 
 // Quad kernel (smm_quad.hip): uniform m = n = k in {5, 6, 13, 23, 26, 32}.
 bool smm_quad_available(int m, int n, int k);
-// Group shape for uniform block size m: 4 x 4 for 23, else 2 x 2 (quads),
-// unless BSM_QUAD_GROUP asks for 2 (2 x 2), 4 (4 x 4) or 42 (4 x 2, size 23)
-// and m has that kernel.
-void quad_shape(int m, int *gr, int *gc);
+// Group shape for uniform block size m and `reuse` products per C block: 4 x 4
+// or 2 x 2 (quads), as measured (smm_quad.hip), unless BSM_QUAD_GROUP asks for
+// 2 (2 x 2), 4 (4 x 4) or 42 (4 x 2, size 23) and m has quads.
+void quad_shape(int m, double reuse, int *gr, int *gc);
 int launch_quad(const SmmArgs &a, hipStream_t s);
-int launch_tile(const SmmArgs &a, unsigned grid, hipStream_t s);   // 4 x 4 groups of size 23 (smm_tile.hip)
+bool smm_tile_available(int m);   // 4 x 4 groups of uniform size m (smm_tile.hip)
+int launch_tile(const SmmArgs &a, unsigned grid, hipStream_t s);
 // Mixed-size groups (smm_mquad.hip): one persistent launch over a.n_quads
 // groups built with paired rows and columns (a.counter: work counter).
 int launch_mquad(const SmmArgs &a, hipStream_t s);

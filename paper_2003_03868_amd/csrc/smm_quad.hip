@@ -401,15 +401,25 @@ bool smm_quad_available(int m, int n, int k) {
     return m == n && n == k && (m == 5 || m == 6 || m == 13 || m == 23 || m == 26 || m == 32);
 }
 
-// Size 23 has the 4 x 4 kernel of smm_tile.hip, whose block products took less
-// time than the quads' at every size measured: 395 -> 314 ms on the square of
-// a settled iterate (2048 block rows, 25% filled), 15.3 -> 13.9 ms at 4.5%,
-// 2.03 -> 1.62 ms at 300 block rows (30%), 0.092 -> 0.082 ms at 64 (50%).
-void quad_shape(int m, int *gr, int *gc) {
+// 4 x 4 groups (smm_tile.hip) share operands four ways but leave waves idle
+// where a group's rows have little in common, so the rule looks at the
+// products per C block.  Whole multiplies, quads and 4 x 4 groups:
+//   23  4 x 4 at every size measured: 2048 block rows, 14.7 products per C
+//       block 16.4 and 15.0 ms, 260 of them 406 and 324 ms; the products alone
+//       2.03 and 1.62 ms at 300 block rows, 0.092 and 0.082 ms at 64;
+//   13  at 10 products per C block 0.58 and 0.58 ms (256 block rows), 15: 6.2
+//       and 6.5 (2048), 34: 9.9 and 8.8 (1024), 92: 26.3 and 22.1;
+//   5   34: 4.4 and 4.6, 92: 10.1 and 9.7, 172: 16.8 and 15.3; 6 alike;
+//   26  34: 47.2 and 48.1, 92: 128.0 and 125.2, 172: 233 and 219;
+//   32  172: 440 and 443 (one group per CU, and rows of 32 doubles fall on
+//       the same LDS banks).
+// The other sizes have no quads.
+void quad_shape(int m, double reuse, int *gr, int *gc) {
     const char *e = getenv("BSM_QUAD_GROUP");
-    const int g = e ? atoi(e) : (m == 23 ? 4 : 2);
+    const bool tile = !smm_quad_available(m, m, m) || m == 23 || (m == 13 && reuse >= 24.0) ||
+                      (m != 13 && m != 32 && reuse >= 64.0);
+    const int g = e && smm_quad_available(m, m, m) ? atoi(e) : (tile ? 4 : 2);
     *gr = *gc = 2;
-    if (m == 5 || m == 6) return;
     if (g == 4) { *gr = 4; *gc = 4; }
     else if (g == 42 && m == 23) { *gr = 4; *gc = 2; }
 }
@@ -445,17 +455,7 @@ int launch_quad(const SmmArgs &a, hipStream_t s) {
         BSM_HIP(hipGetLastError());
         return BSM_OK;
     }
-    if (a.q_gr == 4 && a.q_gc == 4 && a.uni_m == 23) return launch_tile(a, g, s);
-    if (a.q_gr == 4 && a.q_gc == 4) {
-        switch (a.uni_m) {
-            case 13: BSM_LAUNCH((k_smm_f64_quad<13, 4, 4, 16, 8, 1>), g, 1024, 0, s)(a); break;
-            case 26: BSM_LAUNCH((k_smm_f64_quad<26, 4, 4, 16, 4, 1>), g, 1024, 0, s)(a); break;
-            case 32: BSM_LAUNCH((k_smm_f64_quad<32, 4, 4, 16, 4, 1>), g, 1024, 0, s)(a); break;
-            default: set_error("no group-of-sixteen kernel for block size %d", a.uni_m); return BSM_EINVAL;
-        }
-        BSM_HIP(hipGetLastError());
-        return BSM_OK;
-    }
+    if (a.q_gr == 4 && a.q_gc == 4) return launch_tile(a, g, s);
     if (a.q_gr != 2 || a.q_gc != 2) {
         set_error("internal: no %d x %d group kernel for block size %d", a.q_gr, a.q_gc, a.uni_m);
         return BSM_EINVAL;

@@ -1,10 +1,10 @@
-// FP64 block products for uniform block size 23, one workgroup of sixteen
-// waves per 4 x 4 group of C blocks, one C block per wave, with the group's
-// merged product list (built in quad.hip).  Sums and instructions are those
+// FP64 block products for uniform block sizes 4 .. 32, one workgroup of
+// sixteen waves per 4 x 4 group of C blocks, one C block per wave, with the
+// group's merged product list (built in quad.hip).  Sums and instructions are those
 // of the quad kernel (smm_quad.hip): ascending k, V_MFMA_F64_4X4X4_4B_F64,
 // so the results are the same bits.
 //
-// What bounds it: the 2 x 2 quads moved 1.19 operand blocks per product
+// What bounds it (size 23): the 2 x 2 quads moved 1.19 operand blocks per product
 // through L2 (5.1 TB/s of misses on the sign workload's settled products),
 // and the board's power limit held the clock to 2.0 GHz with the matrix
 // cores 58% busy.  A 4 x 4 group moves 0.72 blocks per product.  Four things
@@ -58,7 +58,8 @@ struct TShape {
     static constexpr int PIECES = (B2 * 8 + (B2 & 1) * 8) / 16;   // 16-byte pieces of a staged block
     static constexpr int SLOT = PIECES * 16;                      // LDS bytes of a staged block
     static constexpr int FULL = PIECES / 64, REST = PIECES % 64;  // whole-wave copies, lanes of the last
-    static constexpr int TAIL = (8 * H * S - B2 + 64) * 8;        // padded reads past the last block
+    // padded reads past the last block: A rows up to 8 H, B rows up to 4 KS
+    static constexpr int TAIL = (8 * H * S - B2 + 64) * 8;
 };
 
 // Work item of this workgroup: the items form kXcds contiguous ranges, one
@@ -89,17 +90,25 @@ __device__ inline double t_wave_max(double v) {
 template <int S>
 __device__ inline void stage_block(uint64_t src, uint32_t slot, uint32_t voff) {
     using T = TShape<S>;
-    static_assert(T::FULL == 4 && T::REST > 0, "four whole copies and one part");
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\t"
-                 "global_load_lds_dwordx4 %1, %2\n\t"
-                 "global_load_lds_dwordx4 %1, %2 offset:1024\n\t"
-                 "global_load_lds_dwordx4 %1, %2 offset:2048\n\t"
-                 "global_load_lds_dwordx4 %1, %2 offset:3072\n\t"
-                 "s_mov_b32 m0, %3\n\ts_mov_b64 exec, %5\n\t"
-                 "global_load_lds_dwordx4 %4, %2\n\t"
-                 "s_mov_b64 exec, -1"
-                 :: "s"(slot), "v"(voff), "s"(src), "s"(slot + 4096), "v"(voff + 4096),
-                    "s"((1ull << T::REST) - 1) : "memory");
+#pragma unroll
+    for (int q = 0; q < T::FULL / 4; ++q)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\t"
+                     "global_load_lds_dwordx4 %1, %2\n\t"
+                     "global_load_lds_dwordx4 %1, %2 offset:1024\n\t"
+                     "global_load_lds_dwordx4 %1, %2 offset:2048\n\t"
+                     "global_load_lds_dwordx4 %1, %2 offset:3072"
+                     :: "s"(slot + 4096 * q), "v"(voff + 4096 * q), "s"(src) : "memory");
+#pragma unroll
+    for (int q = T::FULL / 4 * 4; q < T::FULL; ++q)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\t"
+                     "global_load_lds_dwordx4 %1, %2"
+                     :: "s"(slot + 1024 * q), "v"(voff + 1024 * q), "s"(src) : "memory");
+    if constexpr (T::REST > 0)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\ts_mov_b64 exec, %3\n\t"
+                     "global_load_lds_dwordx4 %1, %2\n\t"
+                     "s_mov_b64 exec, -1"
+                     :: "s"(slot + 1024 * T::FULL), "v"(voff + 1024 * T::FULL), "s"(src),
+                        "s"((1ull << T::REST) - 1) : "memory");
 }
 
 // The wave's product of an entry: 4 x 4 x 4 steps in ascending k.  A rows and
@@ -132,18 +141,21 @@ __device__ inline void tile_product(const lds_double *ap, const lds_double *bp, 
 }
 
 // Wave wv owns C block (R, C) = (wv / 4, (wv - wv / 4) mod 4) of the group and
-// (waves 0 .. 7) stages operand wv of every entry (A rows 0 .. 3, B columns
-// 0 .. 3).  Two stages of eight blocks in LDS: entry t is multiplied from
-// stage t mod 2 while entry t + 1 lands in the other.  The barrier of step t
-// follows every wave's wait for its copies of entry t and its last LDS reads
-// of entry t - 1, so after it entry t is whole and the other stage is free.
-template <int S>
-__global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8)))
+// stages operand wv mod 8 (A rows 0 .. 3, B columns 0 .. 3) of every entry
+// (waves 0 .. 7; EPS > 1: waves 0 .. 7 of the even, 8 .. 15 of the odd ones).
+// Two stages of EPS entries of eight blocks in LDS: the EPS entries of a step
+// are multiplied from one while the next EPS land in the other.  The barrier
+// of a step follows every wave's wait for its copies of the step and its last
+// LDS reads of the step before, so after it the step is whole and the other
+// stage is free.  WPE: waves per SIMD (two groups per CU up to size 24, whose
+// stages share its LDS; one above).
+template <int S, int EPS, int WPE>
+__global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
 k_smm_f64_tile(SmmArgs a) {
     using T = TShape<S>;
     constexpr int H = T::H;
     constexpr int G = 4, NOP = 2 * G, NE = NOP / 4;
-    constexpr int STAGE = NOP * T::SLOT;                 // LDS bytes of one staged entry
+    constexpr int ENTRY = NOP * T::SLOT, STAGE = EPS * ENTRY;    // LDS bytes of an entry, of a stage
     __shared__ __align__(16) char lds[2 * STAGE + T::TAIL];
     const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(
         (__attribute__((address_space(3))) char *)lds));
@@ -171,52 +183,61 @@ k_smm_f64_tile(SmmArgs a) {
     const int ne = __builtin_amdgcn_readfirstlane(static_cast<int>(a.q_seg[item + 1] - e0));
     const int *ent = reinterpret_cast<const int *>(a.q_ent + NE * e0);
     // Entries base .. base + 63, one per lane: the wave's row's and column's
-    // operand, and the operand it stages of the entry after (-1: none).
-    const int zown = wv < NOP ? wv : 0;
+    // operand, and the operand it stages of the entry EPS further on (-1: none).
+    const int Z = wv % NOP, first = wv / NOP;
     auto ids = [&](int base, int &ia, int &ib, int &io) {
         const int e = base + lane;
         ia = e < ne ? ent[NOP * e + R] : -1;
         ib = e < ne ? ent[NOP * e + G + C] : -1;
-        io = e + 1 < ne ? ent[NOP * (e + 1) + zown] : -1;
+        io = e + EPS < ne ? ent[NOP * (e + EPS) + Z] : -1;
     };
-    const double *vals = wv < G ? a.a_vals : a.b_vals;
+    const double *vals = Z < G ? a.a_vals : a.b_vals;
     auto source = [&](int id) {                          // 16-byte aligned start of a block
         return (reinterpret_cast<uint64_t>(vals) +
                 static_cast<uint64_t>(static_cast<uint32_t>(id)) * (T::B2 * 8)) & ~15ull;
     };
-    const uint32_t slot = lds0 + wv * T::SLOT;
+    const uint32_t slot = lds0 + Z * T::SLOT;
     const uint32_t voff = lane * 16;
     int ia, ib, io;
     ids(0, ia, ib, io);
-    if (wv < NOP && ne > 0) {
-        const int id = __builtin_amdgcn_readfirstlane(ent[zown]);
-        if (id >= 0) stage_block<S>(source(id), slot, voff);
+#pragma unroll
+    for (int i = 0; i < EPS; ++i) {
+        const int id = i < ne && i % 2 == first ? __builtin_amdgcn_readfirstlane(ent[NOP * i + Z]) : -1;
+        if (id >= 0) stage_block<S>(source(id), slot + i * ENTRY, voff);
     }
     for (int base = 0; base < ne; base += kWave) {
         const uint64_t have = __ballot(ia >= 0 && ib >= 0);
-        const uint64_t mine = wv < NOP ? __ballot(io >= 0) : 0;
-        const int oa = ((lane & 1) ? STAGE : 0) + ((T::B2 & 1) ? (ia & 1) * 8 : 0);
-        const int ob = ((lane & 1) ? STAGE : 0) + ((T::B2 & 1) ? (ib & 1) * 8 : 0);
+        const uint64_t mine = __ballot(io >= 0) &
+                              (EPS == 1 ? (first == 0 ? ~0ull : 0ull)
+                                        : (first == 0 ? 0x5555555555555555ull : 0xaaaaaaaaaaaaaaaaull));
+        const int in = ((lane / EPS) & 1) * STAGE + lane % EPS * ENTRY;
+        const int oa = in + ((T::B2 & 1) ? (ia & 1) * 8 : 0);
+        const int ob = in + ((T::B2 & 1) ? (ib & 1) * 8 : 0);
         const uint64_t sp = source(io);
         const int slo = static_cast<int>(sp), shi = static_cast<int>(sp >> 32);
         ids(base + kWave, ia, ib, io);
         const int n = ne - base < kWave ? ne - base : kWave;
-        for (int t = 0; t < n; ++t) {
+        for (int t = 0; t < n; t += EPS) {
             wait_dma();
             group_barrier();
-            if ((mine >> t) & 1) {
-                const uint64_t src =
-                    static_cast<uint32_t>(__builtin_amdgcn_readlane(slo, t)) |
-                    static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readlane(shi, t))) << 32;
-                stage_block<S>(src, (t & 1) ? slot : slot + STAGE, voff);
-            }
-            if ((have >> t) & 1) {
-                const uint32_t pa = ra0 + __builtin_amdgcn_readlane(oa, t);
-                const uint32_t pb = rb0 + __builtin_amdgcn_readlane(ob, t);
-                tile_product<S>(reinterpret_cast<const lds_double *>(static_cast<uintptr_t>(pa)),
-                                reinterpret_cast<const lds_double *>(static_cast<uintptr_t>(pb)),
-                                klast_ok, acc);
-            }
+            const uint32_t to = (t & EPS) ? slot : slot + STAGE;
+#pragma unroll
+            for (int i = 0; i < EPS; ++i)
+                if ((mine >> (t + i)) & 1) {
+                    const uint64_t src =
+                        static_cast<uint32_t>(__builtin_amdgcn_readlane(slo, t + i)) |
+                        static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readlane(shi, t + i))) << 32;
+                    stage_block<S>(src, to + i * ENTRY, voff);
+                }
+#pragma unroll
+            for (int i = 0; i < EPS; ++i)
+                if ((have >> (t + i)) & 1) {
+                    const uint32_t pa = ra0 + __builtin_amdgcn_readlane(oa, t + i);
+                    const uint32_t pb = rb0 + __builtin_amdgcn_readlane(ob, t + i);
+                    tile_product<S>(reinterpret_cast<const lds_double *>(static_cast<uintptr_t>(pa)),
+                                    reinterpret_cast<const lds_double *>(static_cast<uintptr_t>(pb)),
+                                    klast_ok, acc);
+                }
         }
     }
 
@@ -254,9 +275,24 @@ k_smm_f64_tile(SmmArgs a) {
 
 }  // namespace
 
+// Entries per stage: a barrier serves more of them where the products are
+// short, as long as two groups share a CU's LDS.  Settled squares of 1024
+// block rows (41% filled), 1 / 2 / 4 entries: size 5 18.7 / 14.1 / 12.5 ms, 9
+// 30.7 / 27.5 / 26.1, 13 38.1 / 36.1, 17 80.9 / 79.6.
+constexpr int tile_eps(int s) { return s <= 12 ? 4 : s <= 17 ? 2 : 1; }
+
+bool smm_tile_available(int m) { return m >= 4 && m <= kMaxBlock; }
+
 int launch_tile(const SmmArgs &a, unsigned grid, hipStream_t s) {
     switch (a.uni_m) {
-        case 23: BSM_LAUNCH((k_smm_f64_tile<23>), grid, 1024, 0, s)(a); break;
+#define BSM_TILE(S) \
+        case S: BSM_LAUNCH((k_smm_f64_tile<S, tile_eps(S), (S <= 24 ? 8 : 4)>), grid, 1024, 0, s)(a); break;
+        BSM_TILE(4) BSM_TILE(5) BSM_TILE(6) BSM_TILE(7) BSM_TILE(8) BSM_TILE(9) BSM_TILE(10)
+        BSM_TILE(11) BSM_TILE(12) BSM_TILE(13) BSM_TILE(14) BSM_TILE(15) BSM_TILE(16) BSM_TILE(17)
+        BSM_TILE(18) BSM_TILE(19) BSM_TILE(20) BSM_TILE(21) BSM_TILE(22) BSM_TILE(23) BSM_TILE(24)
+        BSM_TILE(25) BSM_TILE(26) BSM_TILE(27) BSM_TILE(28) BSM_TILE(29) BSM_TILE(30) BSM_TILE(31)
+        BSM_TILE(32)
+#undef BSM_TILE
         default: set_error("no 4 x 4 tile kernel for block size %d", a.uni_m); return BSM_EINVAL;
     }
     BSM_HIP(hipGetLastError());

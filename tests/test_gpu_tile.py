@@ -27,14 +27,16 @@ def _mult(alpha, a, b, beta=0.0, c=None):
     return from_dev(dc), bsm.bsm_last_smm_kernel()
 
 
-@pytest.mark.parametrize("b", [23])
+@pytest.mark.parametrize("b", [4, 5, 6, 7, 9, 12, 13, 14, 16, 17, 18, 22, 23, 24, 25, 26, 29, 31, 32])
 @pytest.mark.parametrize("nbr,nbk,nbc,dens", [
     (1, 1, 1, 1.0), (4, 1, 4, 1.0), (5, 2, 3, 1.0), (4, 63, 4, 1.0), (3, 64, 5, 1.0),
     (4, 65, 4, 0.7), (7, 128, 9, 0.5), (4, 129, 8, 1.0), (6, 131, 6, 0.4)])
 def test_tile_kernel(orc, monkeypatch, b, nbr, nbk, nbc, dens):
     """Against the oracle, and bit for bit against the kernel of one C block
-    per wave (the same products in the same order)."""
+    per wave (the same products in the same order; sizes without a
+    compile-time one: the run-time-shape kernel of 4 x 4 x 4 steps)."""
     monkeypatch.setenv("BSM_QUAD_MIN_REUSE", "0")
+    monkeypatch.setenv("BSM_QUAD_GROUP", "4")
     rng = np.random.default_rng(1000 * nbk + 10 * nbr + b)
     size = lambda n: np.full(n, b)
     a = synth.random_bsr(nbr, nbk, size(nbr), size(nbk), dens, rng)
@@ -44,25 +46,26 @@ def test_tile_kernel(orc, monkeypatch, b, nbr, nbk, nbc, dens):
         got, kernel = _mult(alpha, a, bm, beta, cc)
         assert "k_smm_f64_tile" in kernel
         assert_same_matrix(got, orc.multiply(alpha, a, bm, beta, cc), TOL_FP64_MULTIPLY, "tile")
-        monkeypatch.setenv("BSM_SMM_VARIANT", "2")
+        monkeypatch.setenv("BSM_SMM_VARIANT", "2" if b in (5, 6, 13, 23, 26, 32) else "1")
         one, _ = _mult(alpha, a, bm, beta, cc)
         monkeypatch.delenv("BSM_SMM_VARIANT")
         assert np.array_equal(got.values, one.values)
 
 
-@pytest.mark.parametrize("b", [23])
+@pytest.mark.parametrize("b", [9, 13, 23, 32])
 @pytest.mark.parametrize("bad", [np.nan, np.inf])
 def test_tile_kernel_nonfinite(monkeypatch, b, bad):
     """A block of NaN or Inf reaches the C blocks of its own products and no
     other (what the padding of a block reads is never stored)."""
     monkeypatch.setenv("BSM_QUAD_MIN_REUSE", "0")
+    monkeypatch.setenv("BSM_QUAD_GROUP", "4")
     rng = np.random.default_rng(7)
     a = synth.random_bsr(9, 9, np.full(9, b), np.full(9, b), 0.6, rng)
     off = a.block_offsets()
     for t in (0, 1, a.nnzb // 2, a.nnzb - 1):
         a.values[off[t]:off[t + 1]][:: 1 + t % 3] = bad
     got, _ = _mult(1.0, a, a)
-    monkeypatch.setenv("BSM_SMM_VARIANT", "2")
+    monkeypatch.setenv("BSM_SMM_VARIANT", "2" if b != 9 else "1")
     one, _ = _mult(1.0, a, a)
     assert np.isfinite(one.values).any() and not np.isfinite(one.values).all()
     assert np.array_equal(got.values, one.values, equal_nan=True)
