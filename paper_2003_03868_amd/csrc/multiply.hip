@@ -319,6 +319,28 @@ int multiply(double alpha, Mat &A, Mat &B, double beta, Mat &C, double eps, int 
         use_quad = !table_lookup(A.uni_r, A.uni_r, A.uni_r, &tp) && reuse >= quad_min_reuse() &&
                    static_cast<double>(nprod) * A.uni_r >= 5e5 * quad_min_reuse();
     }
+    // mixed sizes: 4 x 4 groups of consecutive block rows and columns.  Whole
+    // multiplies with the one-block kernels and with groups:
+    //   any sizes ({4, 9, 13, 18, 22, 31}; the persistent kernel): 5e2 products
+    //     0.23 and 0.28 ms, 2e3 0.30 and 0.31, 2e4 0.55 and 0.46, 1.7e5 1.32 and
+    //     0.67; 14.7 products per C block 18.5 and 7.9 ms, 126 250 and 69;
+    //   {5, 13, 23, 26} (sixteen launches, one per class): 4e4 products 0.71 and
+    //     0.40 ms, 5e5 1.73 and 1.01, 1.2e6 1.9 and 2.0; 1024 block rows, 25
+    //     products per C block 18.9 and 15.9 (only sizes 5 and 13: 7.1 and 7.4),
+    //     47 37.6 and 30.0 (14.0 and 12.8), 126 95.7 and 73.1; 4096 block rows,
+    //     9.4 products per C block, 11.2 and 13.2: few entries per group.
+    // Classes that the table has a kernel for keep their launches.
+    bool use_mtile = false;
+    if (prec == BSM_FP64 && tau == 0.0 && variant == kSmmF64Quad && mixed_sizes && nprod > 0) {
+        use_mtile = mixed_ok ? reuse >= 32.0 || nprod <= 600000 : nprod >= 4000;
+        if (const char *e = getenv("BSM_MIXED_TILE")) use_mtile = atoi(e) != 0;
+        for (int b = 0; mixed_ok && b < 16; ++b) {
+            static const int sz[4] = {5, 13, 23, 26};
+            SmmParams tp;
+            if (table_lookup(sz[b / 4], sz[b % 4], 0, &tp) && tp.family != 2) use_mtile = false;
+        }
+        use_quad = use_mtile;
+    }
     // reduced precision: quads where they pay, unless another kernel
     // variant is asked for
     if (prec != BSM_FP64 && variant == kSmmF64Quad && lowp_quad(prec) && A.uni_r && A.uni_c &&
@@ -327,7 +349,8 @@ int multiply(double alpha, Mat &A, Mat &B, double beta, Mat &C, double eps, int 
     // group shape: quads, or other shapes on request (FP64 only); screening
     // runs through the quads' product masks
     int GR = 2, GC = 2;
-    if (use_quad && prec == BSM_FP64 && tau == 0.0) quad_shape(A.uni_r, reuse, &GR, &GC);
+    if (use_mtile) GR = GC = 4;
+    else if (use_quad && prec == BSM_FP64 && tau == 0.0) quad_shape(A.uni_r, reuse, &GR, &GC);
     if (st == BSM_OK && tau > 0.0 && !use_quad) {
         set_error("product screening needs uniform block sizes 5, 6, 13, 23, 26 or 32 and the "
                   "default kernel variant");
@@ -390,6 +413,7 @@ int multiply(double alpha, Mat &A, Mat &B, double beta, Mat &C, double eps, int 
     ma.alpha = alpha; ma.beta = beta;
     ma.sq_out = sq; ma.mx_out = mx; ma.flags = flags;
     ma.max_m = A.max_rbs; ma.max_n = B.max_cbs; ma.max_k = A.max_cbs;
+    ma.nbr = nbr; ma.nbc = B.nbcols;
     ma.uni_m = A.uni_r; ma.uni_n = B.uni_c; ma.uni_k = A.uni_c;
     {
         auto in_set = [](const std::vector<int32_t> &v) {

@@ -77,6 +77,7 @@ struct SmmArgs {
                                 // B(col 0..GC-1) block indices, -1 where absent
     const int64_t *q_order;     // group of work item i (NULL: identity)
     int32_t q_gr, q_gc;         // group shape
+    int32_t nbr, nbc;           // block rows and columns of C
     const int32_t *q_pm;        // product mask per entry (bit GC r + c), NULL: all products
 };
 
@@ -104,6 +105,7 @@ void quad_shape(int m, double reuse, int *gr, int *gc);
 int launch_quad(const SmmArgs &a, hipStream_t s);
 bool smm_tile_available(int m);   // 4 x 4 groups of uniform size m (smm_tile.hip)
 int launch_tile(const SmmArgs &a, unsigned grid, hipStream_t s);
+int launch_mtile(const SmmArgs &a, unsigned grid, hipStream_t s);  // 4 x 4 groups of mixed sizes (smm_mtile.hip)
 // Mixed-size groups (smm_mquad.hip): one persistent launch over a.n_quads
 // groups built with paired rows and columns (a.counter: work counter).
 int launch_mquad(const SmmArgs &a, hipStream_t s);

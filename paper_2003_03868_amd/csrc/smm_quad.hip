@@ -455,6 +455,10 @@ int launch_quad(const SmmArgs &a, hipStream_t s) {
         BSM_HIP(hipGetLastError());
         return BSM_OK;
     }
+    if (!(a.uni_m && a.uni_n && a.uni_k)) {
+        if (a.q_gr != 4 || a.q_gc != 4) { set_error("internal: mixed-size groups are 4 x 4"); return BSM_EINVAL; }
+        return launch_mtile(a, g, s);
+    }
     if (a.q_gr == 4 && a.q_gc == 4) return launch_tile(a, g, s);
     if (a.q_gr != 2 || a.q_gc != 2) {
         set_error("internal: no %d x %d group kernel for block size %d", a.q_gr, a.q_gc, a.uni_m);

@@ -69,3 +69,51 @@ def test_tile_kernel_nonfinite(monkeypatch, b, bad):
     one, _ = _mult(1.0, a, a)
     assert np.isfinite(one.values).any() and not np.isfinite(one.values).all()
     assert np.array_equal(got.values, one.values, equal_nan=True)
+
+
+SIZES = {"basis": (5, 13, 23, 26), "other": (1, 2, 4, 7, 9, 16, 17, 22, 31, 32), "large": (31, 32),
+         "all32": (32, 32)}
+
+
+@pytest.mark.parametrize("sizes", SIZES)
+@pytest.mark.parametrize("nbr,nbk,nbc,dens", [
+    (2, 1, 2, 1.0), (4, 3, 4, 1.0), (5, 64, 3, 0.6), (6, 65, 7, 1.0), (9, 131, 10, 0.4),
+    (17, 40, 21, 0.2)])
+def test_mixed_tile_kernel(orc, monkeypatch, sizes, nbr, nbk, nbc, dens):
+    """Mixed sizes (entries of more than one stage among them: four rows and
+    columns of 32 with k = 32) against the oracle, and bit for bit against
+    the run-time-shape kernel of 4 x 4 x 4 steps."""
+    monkeypatch.setenv("BSM_MIXED_TILE", "1")
+    rng = np.random.default_rng(100 * nbk + nbr)
+    rs, ks, cs = (rng.choice(SIZES[sizes], n) for n in (nbr, nbk, nbc))
+    rs[0], cs[0] = SIZES[sizes][0], SIZES[sizes][-1]
+    if sizes == "all32":
+        rs[-1] = 5                         # not uniform, one group of 32s only
+    a = synth.random_bsr(nbr, nbk, rs, ks, dens, rng)
+    b = synth.random_bsr(nbk, nbc, ks, cs, dens, rng)
+    c = synth.random_bsr(nbr, nbc, rs, cs, 0.5, rng)
+    for alpha, beta, cc in [(1.0, 0.0, None), (-0.5, 1.5, c)]:
+        got, kernel = _mult(alpha, a, b, beta, cc)
+        uniform = len(set(rs)) == len(set(ks)) == len(set(cs)) == 1
+        assert uniform or "k_smm_f64_mtile" in kernel
+        assert_same_matrix(got, orc.multiply(alpha, a, b, beta, cc), TOL_FP64_MULTIPLY, "mixed tile")
+        monkeypatch.setenv("BSM_SMM_VARIANT", "1")
+        one, _ = _mult(alpha, a, b, beta, cc)
+        monkeypatch.delenv("BSM_SMM_VARIANT")
+        assert np.array_equal(got.values, one.values)
+
+
+@pytest.mark.parametrize("bad", [np.nan, np.inf])
+def test_mixed_tile_kernel_nonfinite(monkeypatch, bad):
+    monkeypatch.setenv("BSM_MIXED_TILE", "1")
+    rng = np.random.default_rng(11)
+    s = rng.choice([3, 5, 13, 14, 26, 32], 13)
+    a = synth.random_bsr(13, 13, s, s, 0.6, rng)
+    off = a.block_offsets()
+    for t in (0, 1, a.nnzb // 2, a.nnzb - 1):
+        a.values[off[t]:off[t + 1]][:: 1 + t % 3] = bad
+    got, _ = _mult(1.0, a, a)
+    monkeypatch.setenv("BSM_SMM_VARIANT", "1")
+    one, _ = _mult(1.0, a, a)
+    assert np.isfinite(one.values).any() and not np.isfinite(one.values).all()
+    assert np.array_equal(got.values, one.values, equal_nan=True)
