@@ -32,8 +32,8 @@ namespace {
 constexpr int kTile = 64;      // output tile edge of the dense product
 constexpr int kPad = 32;       // submatrix edges are padded to a multiple of this
 constexpr int kTk = 16;        // k depth staged per LDS stage
-constexpr int kLdA = 68;       // LDS row pitch (doubles) of the k-major A stage
-constexpr int kLdB = 80;       // LDS row pitch (doubles) of the B stage
+
+typedef double d4 __attribute__((ext_vector_type(4)));
 
 struct SubGemm {
     const int4 *tiles;         // (submatrix, tile row, tile column, buffer of X)
@@ -46,16 +46,50 @@ struct SubGemm {
     double *partial;           // mode 0: per tile, sum over its entries of (Y - I)^2
 };
 
+typedef __attribute__((address_space(3))) double lds_double;
+
+// 16 bytes a lane from src + voff to consecutive LDS bytes at `slot`, past
+// the registers.  The compiler does not count these loads; wait_dma() waits
+// for the wave's own.
+__device__ inline void dma16(uint32_t slot, uint32_t voff, const double *src) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %1, %2"
+                 :: "s"(slot), "v"(voff), "s"(reinterpret_cast<uint64_t>(src)) : "memory");
+}
+__device__ inline void wait_dma() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// Workgroup barrier: the wave's own LDS reads are done before it, nothing
+// moves across it.
+__device__ inline void tile_barrier() {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
 // One 64 x 64 tile of D = A B (mode 0: A = B = X, D = Y; mode 1: A = X,
 // B = Y, D = 1.5 X - 0.5 A B into the other X buffer).  Four waves, each a
-// 32 x 32 quarter as 8 x 8 blocks of 4 x 4 on V_MFMA_F64_4X4X4_4B_F64: lane
-// (x, b, y) = lane / 16, lane / 4 % 4, lane % 4 feeds A(i = y, k = x) and
-// B(k = x, j = y) of block b and receives D(i = x, j = y).  A is staged
-// k-major so the eight A operands of a k step are conflict-free LDS reads.
+// 32 x 32 quarter as 2 x 2 tiles of V_MFMA_F64_16X16X4_F64: lane l feeds
+// A(i = l % 16, k = l / 16) and B(k = l / 16, j = l % 16) and receives
+// D(i = 4 r + l / 16, j = l % 16) in register r.  Sums ascend in k.
+//
+// Operands go from memory to LDS past the registers, 16 k at a time and
+// double-buffered: step i + 1 is on its way while step i is multiplied, with
+// one barrier a step.  B's stage holds 16 rows of 64 columns; a step reads
+// four rows at a time, so their 16-column groups are stored turned by the row
+// (group g of row k at g ^ k % 4) and the 64 lanes spread over all banks.
+//
+// SYM (H is its own transpose, so X and Y are too): the launch lists the
+// tiles on and above the diagonal, a quarter below it is skipped, and every
+// element is stored with its mirror image; A(i, k) = X(k, i) is staged from
+// X's rows like B.  Both images hold the same bits: one computed for itself
+// would differ by rounding, a difference that the iteration doubles.
+// Without SYM, A's stage holds 64 rows of 16 k, the 16-byte chunk c of row i
+// at c ^ i / 2 % 8, for the same reason.
+//
 // A tile that reaches past the padded edge is 32 rows or columns wide: the
-// waves of its missing half skip their products and stores, and the
-// staging loads of that half are clamped to addresses inside the square
-// (data that only those idle waves would read).
+// waves of its missing half skip their products and stores, and the staging
+// loads of that half are folded into the square (data that only those idle
+// waves would read).
+template <bool SYM>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_sub_gemm(SubGemm g) {
     // consecutive tiles (one submatrix) on one XCD: workgroups b, b+8, ...
     // share an XCD's L2
@@ -64,7 +98,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
     if (tix >= g.ntiles) return;
     const int4 td = g.tiles[tix];
     const int sub = td.x;
-    const int ld = g.npad[sub];
+    const int ld = g.npad[sub], n = g.ndim[sub];
     const int64_t base = g.base[sub];
     const double *X = (td.w ? g.buf1 : g.buf0) + base;
     const double *Bm = g.mode == 0 ? X : g.ybuf + base;
@@ -72,105 +106,110 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
     const int r0 = td.y * kTile, c0 = td.z * kTile;
     const int vr = min(kTile, ld - r0), vc = min(kTile, ld - c0);   // 32 or 64
 
-    __shared__ double As[2][kTk][kLdA];
-    __shared__ double Bs[2][kTk][kLdB];
+    __shared__ __attribute__((aligned(16))) double stage[2][2][kTk * kTile];   // [buffer][A, B]
     __shared__ double red[4];
 
     const int t = threadIdx.x;
-    const int lane = t & 63, w = t >> 6;
-    const int x = lane >> 4, bb = (lane >> 2) & 3, y = lane & 3;
+    const int lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int l16 = lane & 15, l4 = lane >> 4;
     const int wr = (w >> 1) * 32, wc = (w & 1) * 32;
-    // global -> LDS staging: A rows r0 + t/4, four k from (t%4)*4 (pitch 68:
-    // each transposed store spreads over all banks); B k row t/16, columns
-    // 2c, 2c+1 and 32+2c, 33+2c for c = t%16, so each 16-byte store of a row
-    // is contiguous with its neighbours' and the global reads are two
-    // 256-byte runs per row
-    const int ar = t >> 2, ak = (t & 3) << 2;
-    const int bk = t >> 4, bc = (t & 15) << 1;
-    const double *ga = X + static_cast<int64_t>(r0 + (ar < vr ? ar : 0)) * ld + ak;
-    const double *gb = Bm + static_cast<int64_t>(bk) * ld + c0 + bc;
-    const int bhi = vc > 32 ? 32 : 0;                  // second column half, or a repeat
-    const bool busy = wr < vr && wc < vc;              // wave-uniform
+    const bool busy = wr < vr && wc < vc && !(SYM && r0 + wr > c0 + wc);   // wave-uniform
 
-    // two register sets of staged operands in flight: the loads for k step
-    // i + 3 are issued at step i and written to LDS at step i + 2
-    struct Regs { double2 a0, a1, b0, b1; };
-    auto load = [&](int k, Regs &r) {
-        const double2 *a2 = reinterpret_cast<const double2 *>(ga + k);
-        const double *bp = gb + static_cast<int64_t>(k) * ld;
-        r.a0 = a2[0]; r.a1 = a2[1];
-        r.b0 = *reinterpret_cast<const double2 *>(bp);
-        r.b1 = *reinterpret_cast<const double2 *>(bp + bhi);
-    };
-    auto stage = [&](int buf, const Regs &r) {
-        As[buf][ak + 0][ar] = r.a0.x; As[buf][ak + 1][ar] = r.a0.y;
-        As[buf][ak + 2][ar] = r.a1.x; As[buf][ak + 3][ar] = r.a1.y;
-        *reinterpret_cast<double2 *>(&Bs[buf][bk][bc]) = r.b0;
-        *reinterpret_cast<double2 *>(&Bs[buf][bk][bc + 32]) = r.b1;
-    };
-
-    double acc[8][2];
+    // A wave copies two kilobytes of either stage; byte offsets of the lane's
+    // 16 from (row k or k 0 of the step, first row or column of the tile).
+    const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(
+        (lds_double *)&stage[0][0][0]));
+    uint32_t va[2], vb[2];
 #pragma unroll
-    for (int R = 0; R < 8; ++R) { acc[R][0] = 0.0; acc[R][1] = 0.0; }
-    auto compute = [&](int cur) {
-        if (!busy) return;
-#pragma unroll
-        for (int kk = 0; kk < kTk; kk += 4) {
-            double a[8], b[2];
-#pragma unroll
-            for (int R = 0; R < 8; ++R) a[R] = As[cur][kk + x][wr + 4 * R + y];
-#pragma unroll
-            for (int G = 0; G < 2; ++G) b[G] = Bs[cur][kk + x][wc + 16 * G + 4 * bb + y];
-#pragma unroll
-            for (int R = 0; R < 8; ++R)
-#pragma unroll
-                for (int G = 0; G < 2; ++G)
-                    acc[R][G] = __builtin_amdgcn_mfma_f64_4x4x4f64(a[R], b[G], acc[R][G], 0, 0, 0);
-        }
-    };
-
-    // k steps of kTk up to the edge rounded to kTk (the padding beyond it is
-    // zero, so the remaining steps would add nothing): nk >= 1.  Set s0
-    // carries steps 0, 2, 4, ..., set s1 steps 1, 3, 5, ...; buffer i & 1
-    // holds step i.
-    const int nk = (g.ndim[sub] + kTk - 1) / kTk;
-    Regs s0, s1;
-    load(0, s0);
-    stage(0, s0);
-    if (nk > 1) load(kTk, s1);
-    if (nk > 2) load(2 * kTk, s0);
-    __syncthreads();
-    for (int i = 0; i < nk; i += 2) {
-        compute(0);                                   // step i
-        if (i + 1 < nk) stage(1, s1);                 // step i + 1
-        if (i + 3 < nk) load((i + 3) * kTk, s1);
-        __syncthreads();
-        if (i + 1 < nk) {
-            compute(1);                               // step i + 1
-            if (i + 2 < nk) stage(0, s0);             // step i + 2
-            if (i + 4 < nk) load((i + 4) * kTk, s0);
-            __syncthreads();
+    for (int q = 0; q < 2; ++q) {
+        const int k = (2 * w + q) * 2 + (lane >> 5), c = lane & 31;
+        const int grp = (c >> 3) ^ (k & 3);
+        vb[q] = (static_cast<uint32_t>(k) * ld + (grp & (vc / 16 - 1)) * 16 + (c & 7) * 2) * 8;
+        if (SYM) {
+            va[q] = (static_cast<uint32_t>(k) * ld + (grp & (vr / 16 - 1)) * 16 + (c & 7) * 2) * 8;
+        } else {
+            const int i = (2 * w + q) * 8 + (lane >> 3);
+            va[q] = (static_cast<uint32_t>(i & (vr - 1)) * ld + ((lane & 7) ^ ((i >> 1) & 7)) * 2) * 8;
         }
     }
+    const double *pa = SYM ? X + r0 : X + static_cast<int64_t>(r0) * ld;
+    const double *pb = Bm + c0;
+    const int64_t stepb = static_cast<int64_t>(kTk) * ld, stepa = SYM ? stepb : kTk;
+    auto copy = [&](int buf) {
+        const uint32_t slot = lds0 + buf * (2 * kTk * kTile * 8) + w * 2048;
+        dma16(slot, va[0], pa);
+        dma16(slot + 1024, va[1], pa);
+        dma16(slot + kTk * kTile * 8, vb[0], pb);
+        dma16(slot + kTk * kTile * 8 + 1024, vb[1], pb);
+        pa += stepa;
+        pb += stepb;
+    };
 
-    const int n = g.ndim[sub];
-    double res = 0.0;
+    d4 acc[2][2];
 #pragma unroll
-    for (int R = 0; R < 8 && busy; ++R) {
-        const int r = r0 + wr + 4 * R + x;
+    for (int s = 0; s < 2; ++s)
 #pragma unroll
-        for (int G = 0; G < 2; ++G) {
-            const int c = c0 + wc + 16 * G + 4 * bb + y;
-            const int64_t o = static_cast<int64_t>(r) * ld + c;
-            if (g.mode == 0) {
-                const double v = acc[R][G];
-                D[o] = v;
-                const double d = v - ((r == c && r < n) ? 1.0 : 0.0);
-                res += d * d;
-            } else {
-                D[o] = 1.5 * X[o] - 0.5 * acc[R][G];
+        for (int u = 0; u < 2; ++u) acc[s][u] = d4{0.0, 0.0, 0.0, 0.0};
+    // the lane's operands in a stage (doubles): columns of the quarter's two
+    // 16-wide halves, row l4 of four
+    int oa[2], ob[2];
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        oa[s] = l4 * kTile + ((wr / 16 + s) ^ l4) * 16 + l16;
+        ob[s] = l4 * kTile + ((wc / 16 + s) ^ l4) * 16 + l16;
+    }
+    auto compute = [&](int buf) {
+        const double *A = stage[buf][0], *B = stage[buf][1];
+#pragma unroll
+        for (int kk = 0; kk < kTk / 4; ++kk) {
+            double a[2], b[2];
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                b[s] = B[kk * 4 * kTile + ob[s]];
+                if (SYM) a[s] = A[kk * 4 * kTile + oa[s]];
+                else a[s] = A[(wr + 16 * s + l16) * kTk + ((2 * kk + (l4 >> 1)) ^ (l16 >> 1)) * 2 + (l4 & 1)];
             }
+#pragma unroll
+            for (int s = 0; s < 2; ++s)
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+                    acc[s][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], b[u], acc[s][u], 0, 0, 0);
         }
+    };
+
+    // k steps up to the edge rounded to kTk (the padding beyond it is zero,
+    // so the remaining steps would add nothing): nk >= 1
+    const int nk = (n + kTk - 1) / kTk;
+    copy(0);
+    for (int i = 0; i < nk; ++i) {
+        wait_dma();                       // the wave's part of step i has arrived;
+        tile_barrier();                   // all parts have, and step i - 1 is read
+        if (i + 1 < nk) copy((i + 1) & 1);
+        if (busy) compute(i & 1);
+    }
+
+    double res = 0.0;
+    if (busy) {
+        const bool diag = SYM && r0 + wr == c0 + wc;
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int r = r0 + wr + 16 * s + 4 * e + l4, c = c0 + wc + 16 * u + l16;
+                    if (diag && r > c) continue;
+                    const int64_t o = static_cast<int64_t>(r) * ld + c;
+                    double v = acc[s][u][e];
+                    if (g.mode == 0) {
+                        const double d = v - ((r == c && r < n) ? 1.0 : 0.0);
+                        res += (SYM && r != c) ? 2.0 * (d * d) : d * d;
+                    } else {
+                        v = 1.5 * X[o] - 0.5 * v;
+                    }
+                    D[o] = v;
+                    if (SYM && r != c) D[static_cast<int64_t>(c) * ld + r] = v;
+                }
     }
     if (g.mode == 0) {
 #pragma unroll
@@ -178,6 +217,33 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
         if (lane == 0) red[w] = res;
         __syncthreads();
         if (t == 0) g.partial[tix] = (red[0] + red[1]) + (red[2] + red[3]);
+    }
+}
+
+// Clears `flag` (nonzero beforehand) unless H equals its transpose: every
+// stored block (i, j) has a stored (j, i) with the mirrored values.  One
+// workgroup per block row, a wave per block; NaN is unequal to itself.
+__global__ __launch_bounds__(256) void k_sub_symmetric(const int64_t *row_ptr, const int32_t *col_idx,
+                                                       const int64_t *blk_off, const double *vals,
+                                                       const int32_t *rbs, int32_t *flag) {
+    const int i = blockIdx.x;
+    const int lane = threadIdx.x & 63;
+    const int bi = rbs[i];
+    for (int64_t t = row_ptr[i] + (threadIdx.x >> 6); t < row_ptr[i + 1]; t += 4) {
+        const int j = col_idx[t];
+        int64_t lo = row_ptr[j], hi = row_ptr[j + 1];
+        const int64_t end = hi;
+        while (lo < hi) {
+            const int64_t mid = (lo + hi) >> 1;
+            if (col_idx[mid] < i) lo = mid + 1; else hi = mid;
+        }
+        bool same = lo < end && col_idx[lo] == i;
+        if (same) {
+            const int bj = rbs[j];
+            const double *a = vals + blk_off[t], *b = vals + blk_off[lo];
+            for (int u = lane; u < bi * bj; u += 64) same = same && a[u] == b[u % bj * bi + u / bj];
+        }
+        if (!same) *flag = 0;
     }
 }
 
@@ -333,6 +399,19 @@ int submatrix_density(Mat &H, double mu, const bsm_sign_opts &o, Mat **p_out, bs
     BSM_HIP(hipMemcpyAsync(rp.data(), H.row_ptr, sizeof(int64_t) * (nb + 1), hipMemcpyDeviceToHost, s));
     if (H.nnzb)
         BSM_HIP(hipMemcpyAsync(ci.data(), H.col_idx, sizeof(int32_t) * H.nnzb, hipMemcpyDeviceToHost, s));
+    // whether H is its own transpose: half of every product is then the
+    // mirror image of the other
+    int32_t symmetric = 1;
+    const std::vector<int32_t> yes(1, 1);
+    if (nb > 0) {
+        int32_t *d_flag = nullptr;
+        BSM_TRY(upload(&d_flag, yes, s));
+        hipLaunchKernelGGL(k_sub_symmetric, dim3(nb), dim3(256), 0, s, H.row_ptr, H.col_idx,
+                           H.blk_off, H.values, H.rbs, d_flag);
+        const hipError_t e = hipMemcpyAsync(&symmetric, d_flag, sizeof(int32_t), hipMemcpyDeviceToHost, s);
+        dfree(d_flag, s);
+        BSM_HIP(e);
+    }
     BSM_HIP(hipStreamSynchronize(s));
     std::vector<int64_t> cp(nb + 1, 0);
     for (int64_t t = 0; t < H.nnzb; ++t) cp[ci[t] + 1]++;
@@ -379,6 +458,7 @@ int submatrix_density(Mat &H, double mu, const bsm_sign_opts &o, Mat **p_out, bs
     }
     st->mean_dim = nb ? sum_dim / nb : 0.0;
 
+    const auto gemm = symmetric ? k_sub_gemm<true> : k_sub_gemm<false>;
     const size_t cap = batch_bytes_cap();
     std::vector<std::pair<hipEvent_t, hipEvent_t>> gev;
     int64_t n_noconv = 0;            // submatrices left above tol (every batch still runs)
@@ -447,8 +527,8 @@ int submatrix_density(Mat &H, double mu, const bsm_sign_opts &o, Mat **p_out, bs
         if (rc != BSM_OK) { release(); break; }
 
         // X_0 = (T - mu I) / ||T - mu I||_inf, zero padding
-        if (hipMemsetAsync(buf0, 0, sizeof(double) * tot, s) != hipSuccess ||
-            hipMemsetAsync(buf1, 0, sizeof(double) * tot, s) != hipSuccess) {
+        // (the products write the whole padded squares of the other buffers)
+        if (hipMemsetAsync(buf0, 0, sizeof(double) * tot, s) != hipSuccess) {
             set_error("submatrix: memset failed");
             rc = BSM_EDEVICE;
             release();
@@ -500,7 +580,7 @@ int submatrix_density(Mat &H, double mu, const bsm_sign_opts &o, Mat **p_out, bs
                 const int nt = (npad[q] + kTile - 1) / kTile;
                 tlo.push_back(static_cast<int32_t>(tiles.size()));
                 for (int a = 0; a < nt; ++a)
-                    for (int b = 0; b < nt; ++b) tiles.push_back(make_int4(q, a, b, parity[q]));
+                    for (int b = symmetric ? a : 0; b < nt; ++b) tiles.push_back(make_int4(q, a, b, parity[q]));
                 thi.push_back(static_cast<int32_t>(tiles.size()));
             }
             if (tiles.size() > static_cast<size_t>(INT32_MAX / 2)) {
@@ -535,7 +615,7 @@ int submatrix_density(Mat &H, double mu, const bsm_sign_opts &o, Mat **p_out, bs
             (void)hipEventCreate(&e0);
             (void)hipEventCreate(&e1);
             (void)hipEventRecord(e0, s);
-            hipLaunchKernelGGL(k_sub_gemm, dim3(grid), dim3(256), 0, s, g);       // Y = X X
+            hipLaunchKernelGGL(gemm, dim3(grid), dim3(256), 0, s, g);       // Y = X X
             (void)hipEventRecord(e1, s);
             gev.emplace_back(e0, e1);
             for (int q : active) st->flops += 2.0 * double(ndim[q]) * ndim[q] * ndim[q];
@@ -575,7 +655,7 @@ int submatrix_density(Mat &H, double mu, const bsm_sign_opts &o, Mat **p_out, bs
                 for (int q : next) {
                     const int nt = (npad[q] + kTile - 1) / kTile;
                     for (int a = 0; a < nt; ++a)
-                        for (int b = 0; b < nt; ++b) tiles.push_back(make_int4(q, a, b, parity[q]));
+                        for (int b = symmetric ? a : 0; b < nt; ++b) tiles.push_back(make_int4(q, a, b, parity[q]));
                 }
                 if (hipMemcpyAsync(d_tiles, tiles.data(), sizeof(int4) * tiles.size(),
                                    hipMemcpyHostToDevice, s) != hipSuccess) {
@@ -591,7 +671,7 @@ int submatrix_density(Mat &H, double mu, const bsm_sign_opts &o, Mat **p_out, bs
             (void)hipEventCreate(&f0);
             (void)hipEventCreate(&f1);
             (void)hipEventRecord(f0, s);
-            hipLaunchKernelGGL(k_sub_gemm, dim3(grid2), dim3(256), 0, s, g);
+            hipLaunchKernelGGL(gemm, dim3(grid2), dim3(256), 0, s, g);
             (void)hipEventRecord(f1, s);
             gev.emplace_back(f0, f1);
             for (int q : next) {
