@@ -63,13 +63,26 @@ static double quad_min_reuse() {
     return e ? atof(e) : 8.0;
 }
 
-// Quads for reduced-precision products: BSM_LOWP_QUAD = 1 always, 0 never;
-// default for split-BF16 only (for FP32 products the one-block-per-wave
-// kernel measured faster).
-static bool lowp_quad(int prec) {
+// Groups of C blocks for reduced-precision products (uniform block size m,
+// `reuse` products per C block): BSM_LOWP_QUAD = 1 always, 0 never; by
+// default where they measured faster than one C block per wave.  Building the
+// groups costs a small multiply 0.1 ms, and FP32 products are so short of
+// other work that they gain only where operands are shared by many products.
+// Whole multiplies, one-block kernel and groups, ms:
+//   three parts  172e3 products (100 block rows) size 5 0.37 and 0.41, 13 0.38
+//     and 0.42, 23 0.49 and 0.48, 32 0.65 and 0.50; 743e3 (256) 5 0.65 and 0.58,
+//     23 1.13 and 0.83; 2048 block rows, reuse 9.4, 23 7.1 and 5.1; 18 30 and 20;
+//   two parts    172e3 5 0.35 and 0.41, 23 0.40 and 0.44, 32 0.47 and 0.42; 743e3
+//     5 0.51 and 0.51, 23 0.75 and 0.72; reuse 9.4, 5 2.2 and 2.0, 23 4.2 and 4.1;
+//   FP32         743e3 5 0.43 and 0.52, 23 0.87 and 1.03, 32 1.29 and 1.20; reuse
+//     9.4, 5 1.45 and 1.81, 13 1.88 and 2.03; 18, 5 5.7 and 4.4, 13 7.6 and 6.1,
+//     23 21.3 and 23.3, 26 25.0 and 26.6; 47, 23 31.1 and 29.8, 26 36.3 and 33.6.
+static bool lowp_groups(int prec, int m, double reuse, int64_t nprod) {
     const char *e = getenv("BSM_LOWP_QUAD");
     if (e) return atoi(e) != 0;
-    return prec == BSM_SPLIT_BF16 || prec == BSM_SPLIT_BF16X3;
+    const bool many = nprod >= 400000;
+    if (prec == BSM_FP32) return many && (m == 32 || reuse >= (m <= 13 ? 14.0 : 32.0));
+    return many || static_cast<double>(nprod) * m >= 4e6;
 }
 
 // k segments of the group lists' symbolic walk (one workgroup per row group
@@ -341,15 +354,16 @@ int multiply(double alpha, Mat &A, Mat &B, double beta, Mat &C, double eps, int 
         }
         use_quad = use_mtile;
     }
-    // reduced precision: quads where they pay, unless another kernel
+    // reduced precision: 4 x 4 groups where they pay, unless another kernel
     // variant is asked for
-    if (prec != BSM_FP64 && variant == kSmmF64Quad && lowp_quad(prec) && A.uni_r && A.uni_c &&
-        B.uni_c && smm_lowp_available(A.uni_r, B.uni_c, A.uni_c))
-        use_quad = true;
+    bool lowp_tile = false;
+    if (prec != BSM_FP64 && variant == kSmmF64Quad && A.uni_r && A.uni_c && B.uni_c &&
+        smm_lowp_available(A.uni_r, B.uni_c, A.uni_c))
+        use_quad = lowp_tile = lowp_groups(prec, A.uni_r, reuse, nprod);
     // group shape: quads, or other shapes on request (FP64 only); screening
     // runs through the quads' product masks
     int GR = 2, GC = 2;
-    if (use_mtile) GR = GC = 4;
+    if (use_mtile || lowp_tile) GR = GC = 4;
     else if (use_quad && prec == BSM_FP64 && tau == 0.0) quad_shape(A.uni_r, reuse, &GR, &GC);
     if (st == BSM_OK && tau > 0.0 && !use_quad) {
         set_error("product screening needs uniform block sizes 5, 6, 13, 23, 26 or 32 and the "
@@ -434,11 +448,15 @@ int multiply(double alpha, Mat &A, Mat &B, double beta, Mat &C, double eps, int 
             st = BSM_EINVAL;
         }
         uint32_t *apk = nullptr, *bpk = nullptr;
-        if (st == BSM_OK) st = keep_buf(&apk, lowp_words(A.nvalues, prec));
-        if (st == BSM_OK) st = pack_lowp(A.values, A.nvalues, apk, prec, s);
-        if (st == BSM_OK && &A != &B) {
-            st = keep_buf(&bpk, lowp_words(B.nvalues, prec));
-            if (st == BSM_OK) st = pack_lowp(B.values, B.nvalues, bpk, prec, s);
+        const int size = lowp_tile ? A.uni_r : 0;
+        auto words = [&](const Mat &m) {
+            return size ? lowp_image_words(m.nnzb, size, prec) : lowp_words(m.nvalues, prec);
+        };
+        if (st == BSM_OK) st = keep_buf(&apk, words(A));
+        if (st == BSM_OK) st = pack_operand(A, size, prec, false, apk, s);
+        if (&A != &B || size) {
+            if (st == BSM_OK) st = keep_buf(&bpk, words(B));
+            if (st == BSM_OK) st = pack_operand(B, size, prec, true, bpk, s);
         } else {
             bpk = apk;
         }
@@ -446,7 +464,7 @@ int multiply(double alpha, Mat &A, Mat &B, double beta, Mat &C, double eps, int 
         ma.b_pk = bpk;
         ma.a_pk_n = A.nvalues;
         ma.b_pk_n = B.nvalues;
-        if (pl) { pl->apk = apk; pl->bpk = bpk; }
+        if (pl) { pl->apk = apk; pl->bpk = bpk; pl->image_size = size; }
     }
 
     int32_t n_launch = 0;

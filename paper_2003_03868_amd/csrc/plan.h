@@ -49,9 +49,14 @@ struct MulPlan {
     double *sq = nullptr, *mx = nullptr;  // block norms of the product
     int64_t *kidx = nullptr, *koff = nullptr;   // keep scan and kept offsets
     uint32_t *apk = nullptr, *bpk = nullptr;    // packed reduced-precision operands
+    int image_size = 0;               // > 0: packed as images of blocks of this size
     std::vector<void *> owned;
     std::vector<MulOp> ops;
 };
+
+// A reduced-precision operand packed into `out`: images of its blocks of
+// size image_size for A or B, or (0) its elements in order.
+int pack_operand(const Mat &m, int image_size, int prec, bool b_side, uint32_t *out, hipStream_t s);
 
 // A, B and Cin (NULL when beta == 0) must have the patterns the plan was made
 // for; their values may differ.  Writes the filtered product (p.nval values in

@@ -52,6 +52,11 @@ k_gather_kept(const int64_t *kidx, const int64_t *koff, const int64_t *blk_off,
     for (int64_t e = threadIdx.x; e < len; e += 64) out[dst + e] = vals[src + e];
 }
 
+int pack_operand(const Mat &m, int image_size, int prec, bool b_side, uint32_t *out, hipStream_t s) {
+    if (image_size) return pack_lowp_image(m.values, m.nnzb, image_size, prec, b_side, out, s);
+    return pack_lowp(m.values, m.nvalues, out, prec, s);
+}
+
 int replay_multiply(MulPlan &p, const Mat &A, const Mat &B, const Mat *Cin, double *out,
                     int *flags, hipStream_t s) {
     if (A.nnzb != p.a_nnzb || B.nnzb != p.b_nnzb || A.nvalues != p.a_nval ||
@@ -61,8 +66,8 @@ int replay_multiply(MulPlan &p, const Mat &A, const Mat &B, const Mat *Cin, doub
     }
     if (p.nnzb_u == 0) return BSM_OK;
     if (p.prec != BSM_FP64) {
-        BSM_TRY(pack_lowp(A.values, A.nvalues, p.apk, p.prec, s));
-        if (!p.same_ab) BSM_TRY(pack_lowp(B.values, B.nvalues, p.bpk, p.prec, s));
+        BSM_TRY(pack_operand(A, p.image_size, p.prec, false, p.apk, s));
+        if (p.image_size || !p.same_ab) BSM_TRY(pack_operand(B, p.image_size, p.prec, true, p.bpk, s));
     }
     double *cv = p.compacted ? p.c_vals_u : out;
     for (const MulOp &op : p.ops) {
@@ -76,7 +81,7 @@ int replay_multiply(MulPlan &p, const Mat &A, const Mat &B, const Mat *Cin, doub
         a.c_vals = cv;
         a.flags = flags;
         a.a_pk = p.apk;
-        a.b_pk = p.same_ab ? p.apk : p.bpk;
+        a.b_pk = p.bpk;
         BSM_TRY(run_op(r, s));
     }
     if (p.eps > 0.0) {

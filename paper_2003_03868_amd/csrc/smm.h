@@ -122,6 +122,11 @@ inline int64_t lowp_words(int64_t n, int prec) {
 }
 bool smm_lowp_available(int m, int n, int k);
 int smm_launch_lowp(const SmmArgs &a, hipStream_t s);
-int launch_lowp_quad(const SmmArgs &a, hipStream_t s);   // quads, uniform sizes as above
+// 4 x 4 groups (smm_lowp_tile.hip): images of an operand's blocks (A and B
+// differ), 32-bit words of n of them, the launch.
+int64_t lowp_image_words(int64_t nblocks, int size, int prec);
+int pack_lowp_image(const double *v, int64_t nblocks, int size, int prec, bool b_side, uint32_t *out,
+                    hipStream_t s);
+int launch_lowp_tile(const SmmArgs &a, unsigned grid, hipStream_t s);
 
 }  // namespace bsm

@@ -21,8 +21,10 @@
 //
 // Operands are packed once per multiply: one 32-bit word per element (the
 // FP32 bits, or hi << 16 | lo), and for the three-term split hi << 16 | mid
-// followed by an array of the lo parts (uint16).  Kernels exist for uniform
-// block sizes (compile-time shapes, up to 32).
+// followed by an array of the lo parts (uint16).  The kernels here take one C
+// block per wave, for uniform block sizes (compile-time shapes, up to 32);
+// larger products run over groups of C blocks (smm_lowp_tile.hip).
+#include "bf16_split.h"
 #include "smm.h"
 
 namespace bsm {
@@ -34,20 +36,6 @@ typedef unsigned short us8 __attribute__((ext_vector_type(8)));
 
 // --------------------------------------------------------------- packing
 
-// Round-to-odd double -> float followed by round-to-nearest-even float ->
-// bf16 gives the correctly rounded (RNE) bf16 of the double: the float keeps
-// 24 significant bits, more than the 8 + 2 the second rounding needs.
-__device__ inline uint32_t bf16_rne(double x) {
-    float t = __double2float_rz(x);
-    if (static_cast<double>(t) != x) t = __uint_as_float(__float_as_uint(t) | 1u);
-    uint32_t u = __float_as_uint(t);
-    u += 0x7FFFu + ((u >> 16) & 1u);
-    return u >> 16;
-}
-__device__ inline double bf16_to_double(uint32_t h) {
-    return static_cast<double>(__uint_as_float(h << 16));
-}
-
 __global__ void k_pack_lowp(const double *v, int64_t n, uint32_t *out, int prec) {
     const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
     if (i >= n) return;
@@ -55,16 +43,11 @@ __global__ void k_pack_lowp(const double *v, int64_t n, uint32_t *out, int prec)
     if (prec == BSM_FP32) {
         out[i] = __float_as_uint(__double2float_rn(x));
     } else {
-        // x - hi and r - mid are exact in FP64 (the parts are RNE roundings
-        // of the value they are subtracted from, far above its last bit)
-        const uint32_t hi = bf16_rne(x);
-        const double r = x - bf16_to_double(hi);
-        const uint32_t nxt = bf16_rne(r);
-        out[i] = (hi << 16) | nxt;
-        if (prec == BSM_SPLIT_BF16X3) {
-            const uint32_t lo = bf16_rne(r - bf16_to_double(nxt));
-            reinterpret_cast<unsigned short *>(out + n)[i] = static_cast<unsigned short>(lo);
-        }
+        uint32_t p[3];
+        split_bf16(x, prec == BSM_SPLIT_BF16X3 ? 3 : 2, p);
+        out[i] = (p[0] << 16) | p[1];
+        if (prec == BSM_SPLIT_BF16X3)
+            reinterpret_cast<unsigned short *>(out + n)[i] = static_cast<unsigned short>(p[2]);
     }
 }
 
@@ -335,227 +318,6 @@ k_smm_f32(SmmArgs a) {
         col = 16 * u + r16;
         if (t >= MT || u >= NT) row = 1 << 20;   // tile not present
     });
-}
-
-// ------------------------------------------------------------------ quads
-// The quad scheme of the FP64 path (smm_quad.hip) with the reduced-precision
-// products above: four waves per 2 x 2 quad of C blocks; per entry k wave w
-// stages operand w (A(i_0, k), A(i_1, k), B(k, j_0), B(k, j_1); each read
-// from HBM once) into its LDS slot in the layout the MFMA reads need, and
-// computes C block (w / 2, w % 2) when the entry holds that product.  Each
-// block product is accumulated in FP32 and added into the FP64 sum of its C
-// block, in ascending k, exactly as in the one-block-per-wave kernels.
-__device__ inline int4 lp_uniform4(int4 v) {
-    return make_int4(__builtin_amdgcn_readfirstlane(v.x), __builtin_amdgcn_readfirstlane(v.y),
-                     __builtin_amdgcn_readfirstlane(v.z), __builtin_amdgcn_readfirstlane(v.w));
-}
-
-// T = 0: FP32; T = 2 or 3: split-BF16 with that many parts.  Occupancy
-// target: five waves per SIMD for two parts (96 registers, no spills; 5%
-// faster per sign than four on the 2048-site workload at eps 1e-5; six
-// spill and are slower), four otherwise (three parts need 124 registers).
-template <int S, int T>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T == 2 ? 5 : 4, 8)))
-k_lowp_quad(SmmArgs a) {
-    constexpr bool BF = T >= 2;
-    constexpr int NP = BF ? T : 1;                      // bf16 planes per operand
-    constexpr int B2 = S * S;
-    constexpr int NV = (B2 + kWave - 1) / kWave;
-    constexpr int LDK = 40, PLANE = 32 * LDK;           // split-BF16: [32][LDK] planes
-    constexpr int LDA = 33, LDB = 32, KP = 4 * ((S + 3) / 4);
-    constexpr int FA = 32 * LDA, FB = KP * LDB;          // FP32: A [32][LDA], B [KP][LDB]
-    constexpr int BYTES = BF ? 4 * NP * PLANE * 2 : (2 * FA + 2 * FB) * 4;
-    __shared__ __attribute__((aligned(16))) unsigned char smem[BYTES];
-    __shared__ int4 ebuf[2][64];
-    unsigned short *us = reinterpret_cast<unsigned short *>(smem);
-    float *fs = reinterpret_cast<float *>(smem);
-
-    const int64_t per = (a.n_quads + kXcds - 1) / kXcds;
-    const int64_t it = static_cast<int64_t>(blockIdx.x % kXcds) * per + blockIdx.x / kXcds;
-    if (it >= a.n_quads) return;
-    const int64_t item = a.q_order ? a.q_order[it] : it;
-    const int lane = threadIdx.x % kWave;
-    const int wv = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x / kWave));
-    const int rr = wv >> 1, cc = wv & 1;                // this wave's C block (rr, cc)
-
-    for (int e = threadIdx.x; e < BYTES / 4; e += 256) reinterpret_cast<uint32_t *>(smem)[e] = 0u;
-    // LDS position of element lane + 64 v of this wave's operand (-1: none),
-    // recomputed where it is used (fewer live registers)
-    auto lds_off = [&](int v) {
-        const int e = lane + v * kWave;
-        int o = -1;
-        if (e < B2) {
-            const int i = e / S, j = e % S;            // row, column of the stored block
-            if (BF) o = (wv < 2) ? i * LDK + j : j * LDK + i;
-            else o = (wv < 2) ? wv * FA + i * LDA + j : 2 * FA + (wv - 2) * FB + i * LDB + j;
-        }
-        return o;
-    };
-
-    double acc[16];
-#pragma unroll
-    for (int q = 0; q < 16; ++q) acc[q] = 0.0;
-
-    constexpr int kEntryChunk = 64;
-    const int64_t e0 = a.q_seg[item], ne = a.q_seg[item + 1] - e0;
-    const int4 none = make_int4(-1, -1, -1, -1);
-    auto pick = [](const int4 v, int z) { return z == 0 ? v.x : z == 1 ? v.y : z == 2 ? v.z : v.w; };
-    uint32_t pv[NV];
-    unsigned short pl[T == 3 ? NV : 1];
-    const unsigned short *lo3 = reinterpret_cast<const unsigned short *>(
-        wv < 2 ? a.a_pk + a.a_pk_n : a.b_pk + a.b_pk_n);
-    auto load_block = [&](const int4 en) {
-        const int id = pick(en, wv);
-        if (id >= 0) {
-            const int64_t o0 = static_cast<int64_t>(id) * B2;
-            const uint32_t *g = (wv < 2 ? a.a_pk : a.b_pk) + o0;
-#pragma unroll
-            for (int v = 0; v < NV; ++v)
-                if (v < NV - 1 || lane + v * kWave < B2) pv[v] = g[lane + v * kWave];
-            if (T == 3) {
-#pragma unroll
-                for (int v = 0; v < NV; ++v)
-                    if (v < NV - 1 || lane + v * kWave < B2) pl[v] = lo3[o0 + lane + v * kWave];
-            }
-        }
-    };
-    int4 creg = none;
-    if (wv == 0) {
-        if (lane < ne) ebuf[0][lane] = a.q_ent[e0 + lane];
-        if (kEntryChunk + lane < ne) creg = a.q_ent[e0 + kEntryChunk + lane];
-    }
-    __syncthreads();
-    int4 nxt = none;
-    if (ne > 0) {
-        nxt = lp_uniform4(ebuf[0][0]);
-        load_block(nxt);
-    }
-    const int r32 = lane & 31, h = lane >> 5, r16 = lane & 15, kq = lane >> 4;
-    for (int64_t t = 0; t < ne; ++t) {
-        const int4 cur = nxt;
-        if (pick(cur, wv) >= 0) {
-#pragma unroll
-            for (int v = 0; v < NV; ++v)
-                if (const int o = lds_off(v); o >= 0) {
-                    if (BF) {
-                        const int plane = NP * wv;
-                        us[plane * PLANE + o] = static_cast<unsigned short>(pv[v] >> 16);
-                        us[(plane + 1) * PLANE + o] = static_cast<unsigned short>(pv[v] & 0xFFFFu);
-                        if (T == 3) us[(plane + 2) * PLANE + o] = pl[v];
-                    } else {
-                        fs[o] = __uint_as_float(pv[v]);
-                    }
-                }
-        }
-        const int64_t t1 = t + 1;
-        if ((t1 % kEntryChunk) == 0 && t1 < ne && wv == 0) {
-            ebuf[(t1 / kEntryChunk) & 1][lane] = creg;
-            if (t1 + kEntryChunk + lane < ne) creg = a.q_ent[e0 + t1 + kEntryChunk + lane];
-        }
-        __syncthreads();
-        if (t1 < ne) {
-            nxt = lp_uniform4(ebuf[(t1 / kEntryChunk) & 1][t1 % kEntryChunk]);
-            load_block(nxt);
-        }
-        if (pick(cur, rr) >= 0 && pick(cur, 2 + cc) >= 0) {
-            if (BF) {
-                const unsigned short *as = us + (NP * rr) * PLANE;
-                const unsigned short *bs = us + (NP * (2 + cc)) * PLANE;
-                constexpr int KS = (S + 15) / 16;
-                bf16_split_product<BF ? T : 2, KS, LDK, PLANE>(as, bs, r32 * LDK + 8 * h, acc);
-            } else {
-                const float *sA = fs + rr * FA, *sB = fs + 2 * FA + cc * FB;
-                constexpr int MT = (S + 15) / 16;
-                f4 part[2][2] = {};
-#pragma unroll
-                for (int ks = 0; ks < KP / 4; ++ks) {
-                    float av[2], bv[2];
-#pragma unroll
-                    for (int tt = 0; tt < MT; ++tt) av[tt] = sA[(16 * tt + r16) * LDA + 4 * ks + kq];
-#pragma unroll
-                    for (int u = 0; u < MT; ++u) bv[u] = sB[(4 * ks + kq) * LDB + 16 * u + r16];
-#pragma unroll
-                    for (int tt = 0; tt < MT; ++tt)
-#pragma unroll
-                        for (int u = 0; u < MT; ++u)
-                            part[tt][u] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[tt], bv[u],
-                                                                              part[tt][u], 0, 0, 0);
-                }
-#pragma unroll
-                for (int tt = 0; tt < 2; ++tt)
-#pragma unroll
-                    for (int u = 0; u < 2; ++u)
-#pragma unroll
-                        for (int q = 0; q < 4; ++q)
-                            acc[(tt * 2 + u) * 4 + q] += static_cast<double>(part[tt][u][q]);
-            }
-        }
-        __syncthreads();
-    }
-
-    // epilogue: this wave's C block
-    const int64_t cb = a.q_cblk[4 * item + 2 * rr + cc];
-    if (cb < 0) return;
-    const int64_t co = a.c_blk_off[cb];
-    const double *cin = nullptr;
-    if (a.cin_map) {
-        const int64_t tt = a.cin_map[cb];
-        if (tt >= 0) cin = a.cin_vals + a.cin_blk_off[tt];
-    }
-    double sq = 0.0, mx = 0.0;
-    constexpr int MT = (S + 15) / 16;
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-        int row, col;
-        if (BF) {
-            row = 8 * (q >> 2) + 4 * h + (q & 3);
-            col = r32;
-        } else {
-            const int tile = q >> 2, tt = tile >> 1, u = tile & 1;
-            row = 16 * tt + 4 * kq + (q & 3);
-            col = 16 * u + r16;
-            if (tt >= MT || u >= MT) row = 1 << 20;
-        }
-        if (row < S && col < S) {
-            double v = a.alpha * acc[q];
-            if (cin) v += a.beta * cin[row * S + col];
-            a.c_vals[co + row * S + col] = v;
-            sq += v * v;
-            mx = fmax(mx, fabs(v));
-        }
-    }
-    sq = lp_wave_sum(sq);
-    mx = lp_wave_max(mx);
-    if (lane == 0) {
-        a.sq_out[cb] = sq;
-        a.mx_out[cb] = mx;
-        if (!isfinite(sq)) atomicOr(a.flags, kFlagNonFinite);
-    }
-}
-
-int launch_lowp_quad(const SmmArgs &a, hipStream_t s) {
-    if (a.n_quads <= 0) return BSM_OK;
-    const int64_t per = (a.n_quads + kXcds - 1) / kXcds;
-    const int64_t grid = per * kXcds;
-    if (grid > (1ll << 31) - 1) { set_error("too many quads in one launch"); return BSM_EINVAL; }
-    const unsigned g = static_cast<unsigned>(grid);
-#define BSM_LQ(SZ)                                                            \
-    case SZ:                                                                  \
-        if (a.prec == BSM_SPLIT_BF16) BSM_LAUNCH((k_lowp_quad<SZ, 2>), g, 256, 0, s)(a);\
-        else if (a.prec == BSM_SPLIT_BF16X3) BSM_LAUNCH((k_lowp_quad<SZ, 3>), g, 256, 0, s)(a); \
-        else BSM_LAUNCH((k_lowp_quad<SZ, 0>), g, 256, 0, s)(a);                         \
-        break;
-    switch (a.uni_m) {
-        BSM_LQ(5)
-        BSM_LQ(13)
-        BSM_LQ(23)
-        BSM_LQ(26)
-        BSM_LQ(32)
-        default: set_error("no reduced-precision quad kernel for block size %d", a.uni_m); return BSM_EINVAL;
-    }
-#undef BSM_LQ
-    BSM_HIP(hipGetLastError());
-    return BSM_OK;
 }
 
 bool smm_lowp_available(int m, int n, int k) {

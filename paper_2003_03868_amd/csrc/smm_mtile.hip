@@ -23,6 +23,7 @@
 // waves per SIMD) and, with few entries per group, by the chain of loads that
 // starts a group.  Tried: sixteen waves of one C block, one group per CU and
 // twice the stage: 11 .. 8% slower.
+#include "lds_dma.h"
 #include "smm.h"
 
 namespace bsm {
@@ -30,15 +31,6 @@ namespace bsm {
 namespace {
 
 typedef __attribute__((address_space(3))) double lds_double;
-
-__device__ inline void wait_dma() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-
-// The wave's own LDS reads are done before it, nothing moves across it.
-__device__ inline void group_barrier() {
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-}
 
 __device__ inline int64_t tile_item(int64_t n_items) {
     const int64_t per = (n_items + kXcds - 1) / kXcds;

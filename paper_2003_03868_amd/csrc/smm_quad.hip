@@ -425,7 +425,6 @@ void quad_shape(int m, double reuse, int *gr, int *gc) {
 }
 
 int launch_quad(const SmmArgs &a, hipStream_t s) {
-    if (a.prec != BSM_FP64) return launch_lowp_quad(a, s);
     if (a.n_quads <= 0) return BSM_OK;
     const int64_t per = (a.n_quads + kXcds - 1) / kXcds;
     const int64_t grid = per * kXcds;
@@ -434,6 +433,7 @@ int launch_quad(const SmmArgs &a, hipStream_t s) {
         return BSM_EINVAL;
     }
     const unsigned g = static_cast<unsigned>(grid);
+    if (a.prec != BSM_FP64) return launch_lowp_tile(a, g, s);
     const int w = quad_waves(), eps = quad_stage();
     if (a.q_pm) {
         // product masks (norm screening): quads with four waves (sizes 5, 6: one)

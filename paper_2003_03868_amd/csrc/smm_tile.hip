@@ -30,6 +30,7 @@
 // 0.44 blocks per product, but one group per CU leaves nothing to run while
 // it waits at its barrier), eight waves of 2 x 1 C blocks (322 -> 330 ms),
 // groups ordered in square tiles (346 -> 354 .. 363 ms).
+#include "lds_dma.h"
 #include "smm.h"
 
 namespace bsm {
@@ -38,18 +39,6 @@ namespace {
 
 typedef __attribute__((address_space(3))) double lds_double;
 
-// Copies to LDS past the registers (16 bytes a lane to consecutive LDS bytes
-// at m0) are not counted by the compiler; wait_dma() waits for the wave's own.
-__device__ inline void wait_dma() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-
-// Workgroup barrier: the wave's own LDS reads are done before it, nothing
-// moves across it.
-__device__ inline void group_barrier() {
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-}
-
 template <int S>
 struct TShape {
     static constexpr int B2 = S * S;
@@ -57,7 +46,6 @@ struct TShape {
     static constexpr int KLAST = S - 4 * (KS - 1);                // valid x in the last k-step
     static constexpr int PIECES = (B2 * 8 + (B2 & 1) * 8) / 16;   // 16-byte pieces of a staged block
     static constexpr int SLOT = PIECES * 16;                      // LDS bytes of a staged block
-    static constexpr int FULL = PIECES / 64, REST = PIECES % 64;  // whole-wave copies, lanes of the last
     // padded reads past the last block: A rows up to 8 H, B rows up to 4 KS
     static constexpr int TAIL = (8 * H * S - B2 + 64) * 8;
 };
@@ -77,38 +65,6 @@ __device__ inline double t_wave_sum(double v) {
 __device__ inline double t_wave_max(double v) {
     for (int o = kWave / 2; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, kWave));
     return v;
-}
-
-// A block to the LDS slot: its 16-byte pieces from `src`, its 16-byte aligned
-// start.  Blocks of odd sizes start on 8 bytes: an odd block is copied from
-// one double before it (its even neighbour's last), an even one with one
-// double after it (its neighbour's first or, for the last block, the padding
-// of the allocation, whose size is a multiple of 256 bytes), and the reader
-// adds the block's parity to its offset.  voff = 16 lane; every lane of the
-// wave is active, the last copy runs with the lanes it needs.  The five wait
-// states cover a source address that a lane read has just written.
-template <int S>
-__device__ inline void stage_block(uint64_t src, uint32_t slot, uint32_t voff) {
-    using T = TShape<S>;
-#pragma unroll
-    for (int q = 0; q < T::FULL / 4; ++q)
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\t"
-                     "global_load_lds_dwordx4 %1, %2\n\t"
-                     "global_load_lds_dwordx4 %1, %2 offset:1024\n\t"
-                     "global_load_lds_dwordx4 %1, %2 offset:2048\n\t"
-                     "global_load_lds_dwordx4 %1, %2 offset:3072"
-                     :: "s"(slot + 4096 * q), "v"(voff + 4096 * q), "s"(src) : "memory");
-#pragma unroll
-    for (int q = T::FULL / 4 * 4; q < T::FULL; ++q)
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\t"
-                     "global_load_lds_dwordx4 %1, %2"
-                     :: "s"(slot + 1024 * q), "v"(voff + 1024 * q), "s"(src) : "memory");
-    if constexpr (T::REST > 0)
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\ts_mov_b64 exec, %3\n\t"
-                     "global_load_lds_dwordx4 %1, %2\n\t"
-                     "s_mov_b64 exec, -1"
-                     :: "s"(slot + 1024 * T::FULL), "v"(voff + 1024 * T::FULL), "s"(src),
-                        "s"((1ull << T::REST) - 1) : "memory");
 }
 
 // The wave's product of an entry: 4 x 4 x 4 steps in ascending k.  A rows and
@@ -192,6 +148,11 @@ k_smm_f64_tile(SmmArgs a) {
         io = e + EPS < ne ? ent[NOP * (e + EPS) + Z] : -1;
     };
     const double *vals = Z < G ? a.a_vals : a.b_vals;
+    // Blocks of odd sizes start on 8 bytes: an odd block is copied from one
+    // double before it (its even neighbour's last), an even one with one double
+    // after it (its neighbour's first or, for the last block, the padding of the
+    // allocation, whose size is a multiple of 256 bytes), and the reader adds
+    // the block's parity to its offset.
     auto source = [&](int id) {                          // 16-byte aligned start of a block
         return (reinterpret_cast<uint64_t>(vals) +
                 static_cast<uint64_t>(static_cast<uint32_t>(id)) * (T::B2 * 8)) & ~15ull;
@@ -203,7 +164,7 @@ k_smm_f64_tile(SmmArgs a) {
 #pragma unroll
     for (int i = 0; i < EPS; ++i) {
         const int id = i < ne && i % 2 == first ? __builtin_amdgcn_readfirstlane(ent[NOP * i + Z]) : -1;
-        if (id >= 0) stage_block<S>(source(id), slot + i * ENTRY, voff);
+        if (id >= 0) stage_pieces<T::PIECES>(source(id), slot + i * ENTRY, voff);
     }
     for (int base = 0; base < ne; base += kWave) {
         const uint64_t have = __ballot(ia >= 0 && ib >= 0);
@@ -227,7 +188,7 @@ k_smm_f64_tile(SmmArgs a) {
                     const uint64_t src =
                         static_cast<uint32_t>(__builtin_amdgcn_readlane(slo, t + i)) |
                         static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readlane(shi, t + i))) << 32;
-                    stage_block<S>(src, to + i * ENTRY, voff);
+                    stage_pieces<T::PIECES>(src, to + i * ENTRY, voff);
                 }
 #pragma unroll
             for (int i = 0; i < EPS; ++i)

@@ -24,6 +24,7 @@
 #include <vector>
 
 #include "bsm_internal.h"
+#include "lds_dma.h"
 
 namespace bsm {
 
@@ -49,20 +50,10 @@ struct SubGemm {
 typedef __attribute__((address_space(3))) double lds_double;
 
 // 16 bytes a lane from src + voff to consecutive LDS bytes at `slot`, past
-// the registers.  The compiler does not count these loads; wait_dma() waits
-// for the wave's own.
+// the registers.
 __device__ inline void dma16(uint32_t slot, uint32_t voff, const double *src) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %1, %2"
                  :: "s"(slot), "v"(voff), "s"(reinterpret_cast<uint64_t>(src)) : "memory");
-}
-__device__ inline void wait_dma() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-
-// Workgroup barrier: the wave's own LDS reads are done before it, nothing
-// moves across it.
-__device__ inline void tile_barrier() {
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
 }
 
 // One 64 x 64 tile of D = A B (mode 0: A = B = X, D = Y; mode 1: A = X,
@@ -183,7 +174,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
     copy(0);
     for (int i = 0; i < nk; ++i) {
         wait_dma();                       // the wave's part of step i has arrived;
-        tile_barrier();                   // all parts have, and step i - 1 is read
+        group_barrier();                   // all parts have, and step i - 1 is read
         if (i + 1 < nk) copy((i + 1) & 1);
         if (busy) compute(i & 1);
     }
