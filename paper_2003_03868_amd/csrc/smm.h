@@ -81,6 +81,42 @@ struct SmmArgs {
     const int32_t *q_pm;        // product mask per entry (bit GC r + c), NULL: all products
 };
 
+// Operand block indices of one C block's product stack, taken in order
+// (products 0, 1, 2, ...) by a whole wave: 64 products are read at once, one
+// per lane, the next 64 while these are used, so that an operand load waits
+// for a lane read.  Read per product, the indices and the block offsets
+// behind them were two dependent loads in front of every operand load.  Block
+// products (MI355X) before and now: 6 x 6, 6192 rows, 6.3 products per C block
+// 1.07 and 0.73 ms; 1024 rows, 9.4 per C block: 5 x 5 0.48 and 0.28, 13 x 13
+// 1.07 and 0.90, 23 x 23 2.94 and 2.66; 5 x 5 in FP32 0.45 and 0.38.  More sets
+// of operands in flight (two to four) or four C blocks per workgroup gained
+// nothing more.
+struct StackLane {
+    const int32_t *sa, *sb;
+    int np, lane;
+    int32_t a, b, na, nb;
+    __device__ StackLane(const SmmArgs &args, int64_t p0, int n)
+        : sa(args.stk_a + p0), sb(args.stk_b + p0), np(n), lane(static_cast<int>(threadIdx.x % 64)) {
+        read(0, a, b);
+        read(64, na, nb);
+    }
+    __device__ void read(int base, int32_t &x, int32_t &y) const {
+        x = base + lane < np ? sa[base + lane] : 0;
+        y = base + lane < np ? sb[base + lane] : 0;
+    }
+    // of product p (wave-uniform; called for p = 0, 1, 2, ...)
+    __device__ void get(int p, int &ia, int &ib) {
+        const int i = p % 64;
+        if (i == 0 && p > 0) {
+            a = na;
+            b = nb;
+            read(p + 64, na, nb);
+        }
+        ia = __builtin_amdgcn_readlane(a, i);
+        ib = __builtin_amdgcn_readlane(b, i);
+    }
+};
+
 int smm_launch(const SmmArgs &a, int variant, hipStream_t s);
 // Requested block-product variant (kSmmF64Quad unless BSM_SMM_VARIANT says otherwise).
 int smm_variant();

@@ -221,11 +221,15 @@ k_smm_f64_fixed(SmmArgs a) {
 #pragma unroll
         for (int u = 0; u < S::HC; ++u) acc[t][u] = 0.0;
 
-    const int64_t p0 = a.seg[c - a.c0], p_end = a.seg[c - a.c0 + 1];
+    const int64_t p0 = a.seg[c - a.c0];
+    const int np = __builtin_amdgcn_readfirstlane(static_cast<int>(a.seg[c - a.c0 + 1] - p0));
+    StackLane stk(a, p0, np);
     double pa[S::NA], pb[S::NB];
-    auto prefetch = [&](int64_t p) {
-        const double *ga = a.a_vals + a.a_blk_off[a.stk_a[p]];
-        const double *gb = a.b_vals + a.b_blk_off[a.stk_b[p]];
+    auto prefetch = [&](int p) {
+        int ia, ib;
+        stk.get(p, ia, ib);
+        const double *ga = a.a_vals + static_cast<int64_t>(ia) * (M * K);
+        const double *gb = a.b_vals + static_cast<int64_t>(ib) * (K * N);
 #pragma unroll
         for (int q = 0; q < S::NA; ++q)
             if (q < S::NA - 1 || lane + q * kWave < M * K) pa[q] = ga[lane + q * kWave];
@@ -233,8 +237,8 @@ k_smm_f64_fixed(SmmArgs a) {
         for (int q = 0; q < S::NB; ++q)
             if (q < S::NB - 1 || lane + q * kWave < K * N) pb[q] = gb[lane + q * kWave];
     };
-    if (p0 < p_end) prefetch(p0);
-    for (int64_t p = p0; p < p_end; ++p) {
+    if (np > 0) prefetch(0);
+    for (int p = 0; p < np; ++p) {
 #pragma unroll
         for (int q = 0; q < S::NA; ++q)
             if (q < S::NA - 1 || lane + q * kWave < M * K) sA[lane + q * kWave] = pa[q];
@@ -242,7 +246,7 @@ k_smm_f64_fixed(SmmArgs a) {
         for (int q = 0; q < S::NB; ++q)
             if (q < S::NB - 1 || lane + q * kWave < K * N) sB[lane + q * kWave] = pb[q];
         __syncthreads();
-        if (p + 1 < p_end) prefetch(p + 1);
+        if (p + 1 < np) prefetch(p + 1);
 #pragma unroll
         for (int ks = 0; ks < S::KS; ++ks) {
             double av[S::HR], bv[S::HC];

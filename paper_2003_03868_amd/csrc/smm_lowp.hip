@@ -185,11 +185,15 @@ k_smm_bf16x3(SmmArgs a) {
 #pragma unroll
     for (int q = 0; q < 16; ++q) acc[q] = 0.0;
 
-    const int64_t p0 = a.seg[c - a.c0], p_end = a.seg[c - a.c0 + 1];
+    const int64_t p0 = a.seg[c - a.c0];
+    const int np = __builtin_amdgcn_readfirstlane(static_cast<int>(a.seg[c - a.c0 + 1] - p0));
+    StackLane stk(a, p0, np);
     uint32_t pa[NA], pb[NB];
     unsigned short la[T == 3 ? NA : 1], lb[T == 3 ? NB : 1];
-    auto prefetch = [&](int64_t p) {
-        const int64_t oa0 = a.a_blk_off[a.stk_a[p]], ob0 = a.b_blk_off[a.stk_b[p]];
+    auto prefetch = [&](int p) {
+        int ia, ib;
+        stk.get(p, ia, ib);
+        const int64_t oa0 = static_cast<int64_t>(ia) * (M * K), ob0 = static_cast<int64_t>(ib) * (K * N);
         const uint32_t *ga = a.a_pk + oa0;
         const uint32_t *gb = a.b_pk + ob0;
 #pragma unroll
@@ -203,9 +207,9 @@ k_smm_bf16x3(SmmArgs a) {
             for (int q = 0; q < NB; ++q) lb[q] = (ob[q] >= 0) ? blo3[ob0 + lane + q * kWave] : 0;
         }
     };
-    if (p0 < p_end) prefetch(p0);
+    if (np > 0) prefetch(0);
     __syncthreads();
-    for (int64_t p = p0; p < p_end; ++p) {
+    for (int p = 0; p < np; ++p) {
 #pragma unroll
         for (int q = 0; q < NA; ++q)
             if (oa[q] >= 0) {
@@ -221,7 +225,7 @@ k_smm_bf16x3(SmmArgs a) {
                 if (T == 3) bs[2 * PLANE + ob[q]] = lb[q];
             }
         __syncthreads();
-        if (p + 1 < p_end) prefetch(p + 1);
+        if (p + 1 < np) prefetch(p + 1);
         bf16_split_product<T, KS, LDK, PLANE>(as, bs, r32 * LDK + 8 * h, acc);
         __syncthreads();
     }
@@ -267,19 +271,23 @@ k_smm_f32(SmmArgs a) {
 #pragma unroll
     for (int q = 0; q < 16; ++q) acc[q] = 0.0;
 
-    const int64_t p0 = a.seg[c - a.c0], p_end = a.seg[c - a.c0 + 1];
+    const int64_t p0 = a.seg[c - a.c0];
+    const int np = __builtin_amdgcn_readfirstlane(static_cast<int>(a.seg[c - a.c0 + 1] - p0));
+    StackLane stk(a, p0, np);
     uint32_t pa[NA], pb[NB];
-    auto prefetch = [&](int64_t p) {
-        const uint32_t *ga = a.a_pk + a.a_blk_off[a.stk_a[p]];
-        const uint32_t *gb = a.b_pk + a.b_blk_off[a.stk_b[p]];
+    auto prefetch = [&](int p) {
+        int ia, ib;
+        stk.get(p, ia, ib);
+        const uint32_t *ga = a.a_pk + static_cast<int64_t>(ia) * (M * K);
+        const uint32_t *gb = a.b_pk + static_cast<int64_t>(ib) * (K * N);
 #pragma unroll
         for (int q = 0; q < NA; ++q) pa[q] = (oa[q] >= 0) ? ga[lane + q * kWave] : 0u;
 #pragma unroll
         for (int q = 0; q < NB; ++q) pb[q] = (ob[q] >= 0) ? gb[lane + q * kWave] : 0u;
     };
-    if (p0 < p_end) prefetch(p0);
+    if (np > 0) prefetch(0);
     __syncthreads();
-    for (int64_t p = p0; p < p_end; ++p) {
+    for (int p = 0; p < np; ++p) {
 #pragma unroll
         for (int q = 0; q < NA; ++q)
             if (oa[q] >= 0) sA[oa[q]] = __uint_as_float(pa[q]);
@@ -287,7 +295,7 @@ k_smm_f32(SmmArgs a) {
         for (int q = 0; q < NB; ++q)
             if (ob[q] >= 0) sB[ob[q]] = __uint_as_float(pb[q]);
         __syncthreads();
-        if (p + 1 < p_end) prefetch(p + 1);
+        if (p + 1 < np) prefetch(p + 1);
         f4 part[2][2] = {};
 #pragma unroll
         for (int ks = 0; ks < KP / 4; ++ks) {
