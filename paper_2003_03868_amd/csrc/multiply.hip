@@ -50,17 +50,29 @@ static int quad_tile(const char *name, int dflt) {
     return e ? atoi(e) : dflt;
 }
 
-// Fewest products per C block for the FP64 group kernel.  Its group lists
-// cost a symbolic pass and two more host waits, and the operands a group
-// shares are few when C blocks have few products: on random 20%-dense
-// products of 64-384 block rows (3-15 products per C block, 13 x 13 and
-// 23 x 23 blocks) the one-block kernel took 20-35% less time per call, while
-// on the sign workload (16 and more) the groups are faster.  Below this
-// count the one-block kernel runs, unless BSM_SMM_VARIANT names a kernel or
-// screening needs the groups; BSM_QUAD_MIN_REUSE overrides it.
+// Fewest products per C block for the FP64 group kernels where nothing else
+// is known of the size (BSM_QUAD_MIN_REUSE overrides it).
 static double quad_min_reuse() {
     const char *e = getenv("BSM_QUAD_MIN_REUSE");
     return e ? atof(e) : 8.0;
+}
+
+// FP64 groups for a size m with a one-block kernel of its own, `reuse`
+// products per C block, unless BSM_SMM_VARIANT names a kernel or screening
+// needs the groups.  Their lists cost a symbolic pass and two host waits
+// (0.1 ms, more with many block rows), and what a group saves is operand
+// traffic, which small blocks and few products have little of.  Whole
+// multiplies, groups and one block per wave, ms, at reuse: size 5 (6 alike)
+// 18 4.3 and 3.7, 47 5.6 and 5.3, 92 9.6 and 10.0; 13 15 6.2 and 6.0, 19 4.9 and
+// 4.6, 25 6.3 and 6.9, 92 22 and 30; 23 9 3.3 and 2.8, 11 9.0 and 8.6, 15 14.9
+// and 15.4, 18 21.7 and 24.0; 26 18 43.5 and 39.4, 47 66.4 and 65.0, 92 126 and
+// 133; 32 18 74.0 and 73.4, 25 56.4 and 56.8, 92 242 and 250.  Few products
+// (7e5, reuse 18): 13 0.59 and 0.43, 23 0.96 and 0.74.  The sign iteration (`iter`)
+// has its multiplies from graphs where they run in groups, and keeps to them.
+static bool fp64_groups(int m, double reuse, int64_t nprod, bool iter) {
+    if (iter || getenv("BSM_QUAD_MIN_REUSE")) return reuse >= quad_min_reuse();
+    const double least = m == 23 ? 12.5 : (m == 13 || m == 32) ? 20.0 : 64.0;
+    return reuse >= least && nprod >= 1000000;
 }
 
 // Groups of C blocks for reduced-precision products (uniform block size m,
@@ -314,8 +326,8 @@ int multiply(double alpha, Mat &A, Mat &B, double beta, Mat &C, double eps, int 
         smm_quad_available(A.uni_r, B.uni_c, A.uni_c)) {
         SmmParams tp;
         use_quad = !(table_lookup(A.uni_r, B.uni_c, A.uni_c, &tp) && tp.family != 3);
-        if (use_quad && tau == 0.0 && !getenv("BSM_SMM_VARIANT") && reuse < quad_min_reuse())
-            use_quad = false;
+        if (use_quad && tau == 0.0 && !getenv("BSM_SMM_VARIANT"))
+            use_quad = fp64_groups(A.uni_r, reuse, nprod, sizes != nullptr);
     }
     // the other uniform sizes: 4 x 4 groups instead of the run-time-shape
     // kernel where the table has no choice for the size, C blocks have enough

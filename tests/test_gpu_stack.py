@@ -32,3 +32,24 @@ def test_stacks_around_a_chunk(monkeypatch, prec, b, nk):
         bsm.bsm_multiply(1.0, da.handle, db.handle, 0.0, dc.handle, 0.0, 0, prec)
         out.append(from_dev(dc).values)
     assert np.array_equal(out[0], out[1])
+
+
+@pytest.mark.parametrize("b,blocks,groups", [(5, 100, False), (5, 130, True), (13, 130, True),
+                                             (26, 100, False), (32, 130, True)])
+def test_default_rule(monkeypatch, b, blocks, groups):
+    """Whichever FP64 kernel the default picks, the bits are those of the other."""
+    from paper_2003_03868_amd import bsm
+    monkeypatch.delenv("BSM_SMM_VARIANT", raising=False)
+    rng = np.random.default_rng(b)
+    a = synth.random_bsr(blocks, blocks, np.full(blocks, b), np.full(blocks, b), 0.75, rng)
+    da = to_dev(a)
+    out = []
+    for variant in (None, "2" if groups else "6"):
+        if variant:
+            monkeypatch.setenv("BSM_SMM_VARIANT", variant)
+        dc = bsm.Matrix.empty_like(a.row_blk_size, a.col_blk_size)
+        bsm.bsm_multiply(1.0, da.handle, da.handle, 0.0, dc.handle, 0.0)
+        name = bsm.bsm_last_smm_kernel()
+        assert ("fixed" not in name) == (groups if variant is None else not groups), name
+        out.append(from_dev(dc).values)
+    assert np.array_equal(out[0], out[1])
