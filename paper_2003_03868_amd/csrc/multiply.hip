@@ -349,15 +349,22 @@ int multiply(double alpha, Mat &A, Mat &B, double beta, Mat &C, double eps, int 
     //   any sizes ({4, 9, 13, 18, 22, 31}; the persistent kernel): 5e2 products
     //     0.23 and 0.28 ms, 2e3 0.30 and 0.31, 2e4 0.55 and 0.46, 1.7e5 1.32 and
     //     0.67; 14.7 products per C block 18.5 and 7.9 ms, 126 250 and 69;
-    //   {5, 13, 23, 26} (sixteen launches, one per class): 4e4 products 0.71 and
-    //     0.40 ms, 5e5 1.73 and 1.01, 1.2e6 1.9 and 2.0; 1024 block rows, 25
-    //     products per C block 18.9 and 15.9 (only sizes 5 and 13: 7.1 and 7.4),
-    //     47 37.6 and 30.0 (14.0 and 12.8), 126 95.7 and 73.1; 4096 block rows,
-    //     9.4 products per C block, 11.2 and 13.2: few entries per group.
+    //   {5, 13, 23, 26} (a launch per (m, n) class): all four sizes, 7e4 products
+    //     1.18 and 0.60 ms, 4e5 1.34 and 0.81, 1.1e6 1.74 and 1.66, 1.8e6 2.2 and
+    //     2.6; only 5 and 13 7e4 0.49 and 0.43, 3e5 0.54 and 0.53, 7e5 0.69 and 0.77;
+    //     1024 block rows, four sizes, 15 products per C block 6.8 and 8.2, 34 21.3
+    //     and 22.0, 47 31.0 and 30.1, 126 83 and 73; 5 and 13 47 10.6 and 12.6, 126
+    //     27.8 and 28.5; 13 and 23 47 30.3 and 29.9, 126 84 and 71.
     // Classes that the table has a kernel for keep their launches.
     bool use_mtile = false;
     if (prec == BSM_FP64 && tau == 0.0 && variant == kSmmF64Quad && mixed_sizes && nprod > 0) {
-        use_mtile = mixed_ok ? reuse >= 32.0 || nprod <= 600000 : nprod >= 4000;
+        auto distinct = [](const std::vector<int32_t> &v) {
+            uint32_t m = 0;
+            for (int32_t b : v) m |= 1u << b;
+            return __builtin_popcount(m);
+        };
+        use_mtile = mixed_ok ? reuse >= 64.0 || nprod <= 50000 * distinct(A.h_rbs) * distinct(B.h_cbs)
+                             : nprod >= 4000;
         if (const char *e = getenv("BSM_MIXED_TILE")) use_mtile = atoi(e) != 0;
         for (int b = 0; mixed_ok && b < 16; ++b) {
             static const int sz[4] = {5, 13, 23, 26};

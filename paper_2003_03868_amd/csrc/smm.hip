@@ -302,17 +302,39 @@ k_smm_f64_fixed(SmmArgs a) {
 // Per-(m, n)-class FP64 kernel with run-time k: M and N are compile-time, the
 // k of each product is read from the stack.  Launched once per class over the
 // class's contiguous range of the class-sorted work list.  LDS holds the two
-// operand blocks contiguously (as in HBM) plus a zeroed tail; lanes whose k
-// index passes the product's k read zero.
+// operand blocks contiguously (as in HBM); lanes whose k index passes the
+// product's k read zero.
+//
+// What bounds it (4096 block rows, 3.4e7 products, 14.7 per C block): neither
+// the matrix cores (busy 26%) nor memory (the order of the work list makes no
+// difference) but the instructions around a product: 131 scalar ones and 49
+// branches.  With the loads of each k written out without masks, the
+// metadata in registers instead of LDS (which leaves room for more waves), no
+// clearing of the tail, and the paths of each k one after the other instead of
+// a switch that copied the accumulators, the sixteen classes took 20.9 ms
+// instead of 27.0 (26 x 26 3.58 and 2.77, 5 x 5 0.54 and 0.46).
 constexpr int kClassKmax = 26;   // largest k of the class set {5, 13, 23, 26}
 
+// Load, staging and multiply of one product with k known at compile time (the
+// class set's k in {5, 13, 23, 26}): fully unrolled, only the last k-step
+// masked.  LDS layout: A (M x K) then B (K x N), row-major; padded rows and
+// columns read neighbouring data that reaches only accumulator elements that
+// are never stored.  Lanes past a block's end load its last value, so that no
+// load needs a mask.
+template <int M, int N, int K, int NA, int NB>
+__device__ inline void class_load(const double *ga, const double *gb, int lane, double (&pa)[NA],
+                                  double (&pb)[NB]) {
+#pragma unroll
+    for (int v = 0; v < NA; ++v)
+        if (v * kWave < M * K)
+            pa[v] = ga[(v + 1) * kWave <= M * K ? lane + v * kWave : min(lane + v * kWave, M * K - 1)];
+#pragma unroll
+    for (int v = 0; v < NB; ++v)
+        if (v * kWave < K * N)
+            pb[v] = gb[(v + 1) * kWave <= K * N ? lane + v * kWave : min(lane + v * kWave, K * N - 1)];
+}
 
-// Staging and multiply of one product with k known at compile time (the
-// class set's k in {5, 13, 23, 26}): fully unrolled k-steps, only the last
-// one masked.  Layout as in k_smm_f64_class: A (M x K) then B (K x N),
-// row-major, then the zeroed tail; padded rows/columns read neighbouring
-// data that reaches only accumulator elements that are never stored.
-template <int M, int N, int K, int NA, int NB, int TAIL>
+template <int M, int N, int K, int NA, int NB>
 __device__ inline void class_stage(double *sm, int lane, const double (&pa)[NA],
                                    const double (&pb)[NB]) {
     double *sA = sm, *sB = sm + M * K;
@@ -322,9 +344,6 @@ __device__ inline void class_stage(double *sm, int lane, const double (&pa)[NA],
 #pragma unroll
     for (int v = 0; v < NB; ++v)
         if (v * kWave < K * N && lane + v * kWave < K * N) sB[lane + v * kWave] = pb[v];
-#pragma unroll
-    for (int e = M * K + K * N; e < M * K + K * N + TAIL; e += kWave)
-        if (e + lane < M * K + K * N + TAIL) sm[e + lane] = 0.0;
 }
 
 template <int M, int N, int K, int HR, int HC>
@@ -355,24 +374,18 @@ __device__ inline void class_compute(const double *sm, int bh, int bw, int x, in
     }
 }
 
-// LDS of one class C block: the two operand blocks, a zeroed tail and the
-// product metadata of the per-class kernel.
+// LDS of one class C block: the two operand blocks and what the padded reads
+// past them reach.
 template <int N>
 constexpr int class_tail() { return 4 * kClassKmax + 8 * N + 8; }
-constexpr int kMetaChunk = 64;
-struct ClassMeta {
-    int64_t off[2][2][kMetaChunk];   // [buffer][A, B][product]
-    int32_t k[2][kMetaChunk];
-};
 
 // C block c of class (M, N) on one wavefront (the per-class kernel's body).
 template <int M, int N>
-__device__ inline void class_cblock(const SmmArgs &a, int64_t c, double *sm, ClassMeta &md) {
+__device__ inline void class_cblock(const SmmArgs &a, int64_t c, double *sm) {
     constexpr int MT = (M + 3) / 4, NT = (N + 3) / 4;
     constexpr int HR = (MT + 1) / 2, HC = (NT + 1) / 2;
     constexpr int NA = (M * kClassKmax + kWave - 1) / kWave;
     constexpr int NB = (kClassKmax * N + kWave - 1) / kWave;
-    constexpr int TAIL = class_tail<N>();
     const int lane = threadIdx.x;
     const int x = lane >> 4, blk = (lane >> 2) & 3, y = lane & 3;
     const int bh = blk >> 1, bw = blk & 1;
@@ -381,97 +394,93 @@ __device__ inline void class_cblock(const SmmArgs &a, int64_t c, double *sm, Cla
     for (int t = 0; t < HR; ++t)
 #pragma unroll
         for (int u = 0; u < HC; ++u) acc[t][u] = 0.0;
-    // Per-product metadata (operand offsets and k) is fetched for 64 products
-    // at once, one product per lane, and kept in LDS (double-buffered; the next
-    // chunk waits in registers), so the operand loads of product p + 1 never
-    // wait on the chain stack -> block index -> offset of the same iteration.
-    auto &m_off = md.off;
-    auto &m_k = md.k;
-    const int64_t p0 = a.seg[c - a.c0], np = a.seg[c - a.c0 + 1] - p0;
-    int64_t r_aoff = 0, r_boff = 0;
-    int r_k = 0;
-    auto meta = [&](int64_t q, int64_t &ao, int64_t &bo, int &kk) {   // q < np
+    // Per-product metadata (operand offsets and k) is read for 64 products at
+    // once, one product per lane, the next 64 while these are used, so that
+    // the operand loads of a product wait for lane reads only.
+    const int64_t p0 = a.seg[c - a.c0];
+    const int np = __builtin_amdgcn_readfirstlane(static_cast<int>(a.seg[c - a.c0 + 1] - p0));
+    int64_t ao = 0, bo = 0, nao = 0, nbo = 0;
+    int kk = 0, nkk = 0;
+    auto meta = [&](int q, int64_t &o1, int64_t &o2, int &k) {
+        if (q >= np) return;
         const int32_t ta = a.stk_a[p0 + q];
-        ao = a.a_blk_off[ta];
-        bo = a.b_blk_off[a.stk_b[p0 + q]];
-        kk = a.k_size[a.a_col_idx[ta]];
+        o1 = a.a_blk_off[ta];
+        o2 = a.b_blk_off[a.stk_b[p0 + q]];
+        k = a.k_size[a.a_col_idx[ta]];
     };
-    if (lane < np) {
-        int64_t ao, bo;
-        int kk;
-        meta(lane, ao, bo, kk);
-        m_off[0][0][lane] = ao;
-        m_off[0][1][lane] = bo;
-        m_k[0][lane] = kk;
-    }
-    if (kMetaChunk + lane < np) meta(kMetaChunk + lane, r_aoff, r_boff, r_k);
-    __syncthreads();
+    meta(lane, ao, bo, kk);
+    if (np > kWave) meta(lane + kWave, nao, nbo, nkk);
+    auto lane64 = [](int64_t v, int i) {
+        return static_cast<int64_t>(
+            static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v), i)) |
+            static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v >> 32), i))) << 32);
+    };
     double pa[NA], pb[NB];
+    const double *gA = nullptr, *gB = nullptr;
     int kn = 0;
-    auto prefetch = [&](int64_t q) {           // operand blocks of product q (from LDS metadata)
-        const int buf = static_cast<int>((q / kMetaChunk) & 1), i = static_cast<int>(q % kMetaChunk);
-        kn = __builtin_amdgcn_readfirstlane(m_k[buf][i]);
-        const double *gA = a.a_vals + uniform64(m_off[buf][0][i]);
-        const double *gB = a.b_vals + uniform64(m_off[buf][1][i]);
-#pragma unroll
-        for (int v = 0; v < NA; ++v)
-            if (lane + v * kWave < M * kn) pa[v] = gA[lane + v * kWave];
-#pragma unroll
-        for (int v = 0; v < NB; ++v)
-            if (lane + v * kWave < kn * N) pb[v] = gB[lane + v * kWave];
+    auto prefetch = [&](int q) {               // operand blocks of product q (0, 1, 2, ...)
+        const int i = q % kWave;
+        if (i == 0 && q > 0) {
+            ao = nao; bo = nbo; kk = nkk;
+            meta(q + kWave + lane, nao, nbo, nkk);
+        }
+        kn = __builtin_amdgcn_readlane(kk, i);
+        gA = a.a_vals + lane64(ao, i);
+        gB = a.b_vals + lane64(bo, i);
+        int k = kn;
+        if (k == 26) class_load<M, N, 26, NA, NB>(gA, gB, lane, pa, pb);
+        asm volatile("" : "+s"(k));
+        if (k == 23) class_load<M, N, 23, NA, NB>(gA, gB, lane, pa, pb);
+        asm volatile("" : "+s"(k));
+        if (k == 13) class_load<M, N, 13, NA, NB>(gA, gB, lane, pa, pb);
+        asm volatile("" : "+s"(k));
+        if (k == 5) class_load<M, N, 5, NA, NB>(gA, gB, lane, pa, pb);
     };
     if (np > 0) prefetch(0);
-    for (int64_t t = 0; t < np; ++t) {
-        const int k = kn;
+    for (int t = 0; t < np; ++t) {
+        int k = kn;
         double *sA = sm, *sB = sm + M * k;
-        switch (k) {
-            case 5: class_stage<M, N, 5, NA, NB, TAIL>(sm, lane, pa, pb); break;
-            case 13: class_stage<M, N, 13, NA, NB, TAIL>(sm, lane, pa, pb); break;
-            case 23: class_stage<M, N, 23, NA, NB, TAIL>(sm, lane, pa, pb); break;
-            case 26: class_stage<M, N, 26, NA, NB, TAIL>(sm, lane, pa, pb); break;
-            default:
-#pragma unroll
-                for (int v = 0; v < NA; ++v)
-                    if (lane + v * kWave < M * k) sA[lane + v * kWave] = pa[v];
-#pragma unroll
-                for (int v = 0; v < NB; ++v)
-                    if (lane + v * kWave < k * N) sB[lane + v * kWave] = pb[v];
-                for (int e = M * k + k * N + lane; e < M * k + k * N + TAIL; e += kWave) sm[e] = 0.0;
-        }
-        const int64_t t1 = t + 1;
-        if ((t1 % kMetaChunk) == 0 && t1 < np) {
-            const int buf = static_cast<int>((t1 / kMetaChunk) & 1);
-            m_off[buf][0][lane] = r_aoff;
-            m_off[buf][1][lane] = r_boff;
-            m_k[buf][lane] = r_k;
-            if (t1 + kMetaChunk + lane < np) meta(t1 + kMetaChunk + lane, r_aoff, r_boff, r_k);
+        if (k == 26) class_stage<M, N, 26, NA, NB>(sm, lane, pa, pb);
+        asm volatile("" : "+s"(k));
+        if (k == 23) class_stage<M, N, 23, NA, NB>(sm, lane, pa, pb);
+        asm volatile("" : "+s"(k));
+        if (k == 13) class_stage<M, N, 13, NA, NB>(sm, lane, pa, pb);
+        asm volatile("" : "+s"(k));
+        if (k == 5) class_stage<M, N, 5, NA, NB>(sm, lane, pa, pb);
+        asm volatile("" : "+s"(k));
+        if (k != 5 && k != 13 && k != 23 && k != 26) {   // not prefetched
+#pragma unroll 1
+            for (int e = lane; e < M * k; e += kWave) sA[e] = gA[e];
+#pragma unroll 1
+            for (int e = lane; e < k * N; e += kWave) sB[e] = gB[e];
         }
         __syncthreads();
-        if (t1 < np) prefetch(t1);
-        switch (k) {
-            case 5: class_compute<M, N, 5, HR, HC>(sm, bh, bw, x, y, acc); break;
-            case 13: class_compute<M, N, 13, HR, HC>(sm, bh, bw, x, y, acc); break;
-            case 23: class_compute<M, N, 23, HR, HC>(sm, bh, bw, x, y, acc); break;
-            case 26: class_compute<M, N, 26, HR, HC>(sm, bh, bw, x, y, acc); break;
-            default: {
-                int ra[HR];
-#pragma unroll
-                for (int t = 0; t < HR; ++t) ra[t] = (4 * (bh * HR + t) + y) * k + x;
-                const int rb = x * N + 4 * bw * HC + y;
+        if (t + 1 < np) prefetch(t + 1);
+        // one `if` after the other: as a switch, the accumulators of every
+        // path are copied to common registers
+        if (k == 26) class_compute<M, N, 26, HR, HC>(sm, bh, bw, x, y, acc);
+        asm volatile("" : "+s"(k));
+        if (k == 23) class_compute<M, N, 23, HR, HC>(sm, bh, bw, x, y, acc);
+        asm volatile("" : "+s"(k));
+        if (k == 13) class_compute<M, N, 13, HR, HC>(sm, bh, bw, x, y, acc);
+        asm volatile("" : "+s"(k));
+        if (k == 5) class_compute<M, N, 5, HR, HC>(sm, bh, bw, x, y, acc);
+        asm volatile("" : "+s"(k));
+        if (k != 5 && k != 13 && k != 23 && k != 26) {
+            const int ra = (4 * bh * HR + y) * k + x, rb = x * N + 4 * bw * HC + y;
 #pragma unroll 1
-                for (int ks = 0; 4 * ks < k; ++ks) {
-                    const bool ok = 4 * ks + x < k;
-                    double av[HR], bv[HC];
+            for (int ks = 0; 4 * ks < k; ++ks) {
+                const bool ok = 4 * ks + x < k;
+                double av[HR], bv[HC];
 #pragma unroll
-                    for (int t = 0; t < HR; ++t) av[t] = ok ? sA[ra[t] + 4 * ks] : 0.0;
+                for (int t = 0; t < HR; ++t) av[t] = ok ? sA[ra + 4 * t * k + 4 * ks] : 0.0;
 #pragma unroll
-                    for (int u = 0; u < HC; ++u) bv[u] = ok ? sB[rb + 4 * u + 4 * ks * N] : 0.0;
+                for (int u = 0; u < HC; ++u) bv[u] = ok ? sB[rb + 4 * u + 4 * ks * N] : 0.0;
 #pragma unroll
-                    for (int t = 0; t < HR; ++t)
+                for (int t = 0; t < HR; ++t)
 #pragma unroll
-                        for (int u = 0; u < HC; ++u)
-                            acc[t][u] = __builtin_amdgcn_mfma_f64_4x4x4f64(av[t], bv[u], acc[t][u], 0, 0, 0);
-                }
+                    for (int u = 0; u < HC; ++u)
+                        acc[t][u] = __builtin_amdgcn_mfma_f64_4x4x4f64(av[t], bv[u], acc[t][u], 0, 0, 0);
             }
         }
         __syncthreads();                       // this product's reads are done
@@ -505,14 +514,19 @@ __device__ inline void class_cblock(const SmmArgs &a, int64_t c, double *sm, Cla
     }
 }
 
+// Register budget: the waves per SIMD that the LDS of a C block allows.
 template <int M, int N>
-__global__ void __launch_bounds__(64)
+constexpr int class_lds() { return M * kClassKmax + kClassKmax * N + class_tail<N>(); }
+template <int M, int N>
+constexpr int class_waves() { return std::min(6, 160 * 1024 / (8 * class_lds<M, N>()) / 4); }
+
+template <int M, int N>
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(class_waves<M, N>(), 8)))
 k_smm_f64_class(SmmArgs a) {
-    __shared__ double sm[M * kClassKmax + kClassKmax * N + class_tail<N>()];
-    __shared__ ClassMeta md;
+    __shared__ double sm[class_lds<M, N>()];
     const int64_t item = xcd_item(a.nC);
     if (item >= a.nC) return;
-    class_cblock<M, N>(a, a.worklist[a.c0 + item], sm, md);
+    class_cblock<M, N>(a, a.worklist[a.c0 + item], sm);
 }
 
 int class_of_size(int b) { return b == 5 ? 0 : b == 13 ? 1 : b == 23 ? 2 : b == 26 ? 3 : -1; }
