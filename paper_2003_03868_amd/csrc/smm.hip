@@ -29,14 +29,6 @@ __device__ inline int64_t xcd_item(int64_t n_items) {
     return static_cast<int64_t>(blockIdx.x % kXcds) * per + blockIdx.x / kXcds;
 }
 
-// A value that is the same in every lane (read from LDS at a uniform
-// address), made wave-uniform for the compiler.
-__device__ inline int64_t uniform64(int64_t v) {
-    const uint32_t lo = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(v)));
-    const uint32_t hi = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(v >> 32)));
-    return static_cast<int64_t>((static_cast<uint64_t>(hi) << 32) | lo);
-}
-
 __device__ inline double wave_sum(double v) {
     for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
     return v;

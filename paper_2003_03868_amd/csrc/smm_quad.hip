@@ -1,6 +1,6 @@
 // FP64 block products for uniform block sizes, one workgroup per GR x GC
-// group of C blocks (2 x 2: quads, the default; 4 x 4 and 4 x 2 on request)
-// with a merged product list (built in quad.hip).
+// group of C blocks (2 x 2: quads; 4 x 2 on request; 4 x 4 groups run in
+// smm_tile.hip) with a merged product list (built in quad.hip).
 //
 // Per entry k the workgroup stages the (up to) GR + GC operand blocks
 // A(i_r, k), B(k, j_c) in LDS exactly as they sit in HBM, each read from HBM
@@ -191,10 +191,7 @@ __device__ inline void quad_store(const SmmArgs &a, int64_t item, int R0, int C0
 // W wavefronts per group.  Quads: W = 1, the wave computes all four C
 // blocks; W = 2, wave w computes the two C blocks of row w and stages
 // A(i_w, k), B(k, j_w); W = 4, wave w computes C block (w / 2, w % 2) and
-// stages operand w.  Groups of sixteen: W = 16, wave w computes C block
-// (w / 4, w % 4), and waves w and w + 8 stage the two halves of operand
-// w % 8 (with eight waves, two C blocks each, the register demand spills).
-// 4 x 2 groups: W = 8, wave w computes C block (w / 2, w % 2); waves 0..5
+// stages operand w.  4 x 2 groups: W = 8, wave w computes C block (w / 2, w % 2); waves 0..5
 // stage the four A and two B blocks.
 // WPE: the occupancy (waves per SIMD) the register allocation aims for.
 // MK: entries carry product masks (norm screening, a.q_pm).
@@ -212,7 +209,7 @@ k_smm_f64_quad(SmmArgs a) {
     constexpr int NVP = (Q::NV + WPO - 1) / WPO;  // register slots of one staged part
     constexpr int NE = (NOP + 3) / 4;           // int4 per entry
     constexpr int SLOT = NOP * Q::B2;           // LDS doubles of one staged entry
-    static_assert(NE <= 2 && GC % NC == 0, "group shapes up to 4 x 4");
+    static_assert(NE <= 2 && GC % NC == 0, "group shapes up to 4 x 2");
     static_assert(NR * NC * W == GR * GC, "waves must tile the group");
     static_assert(W > NOP || NOP % W == 0, "operands must split evenly over the waves");
     __shared__ double sm[EPS * SLOT + Q::TAIL];
@@ -383,8 +380,8 @@ k_smm_f64_quad(SmmArgs a) {
 
 }  // namespace
 
-// Wavefronts per quad (1, 2 or 4, measured best 4; groups of sixteen always
-// use 16); BSM_QUAD_WAVES overrides the default.
+// Wavefronts per quad (1, 2 or 4, measured best 4); BSM_QUAD_WAVES overrides
+// the default.
 static int quad_waves() {
     const char *e = getenv("BSM_QUAD_WAVES");
     const int w = e ? atoi(e) : 4;
