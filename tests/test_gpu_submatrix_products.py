@@ -40,9 +40,9 @@ def _blocks(d, nb, b):
 
 
 # edges: 1, below and at the k depth, one past 32 and 64, 32 over a tile, the
-# largest with four tiles
+# largest with four tiles, more than 64 block columns
 @pytest.mark.parametrize("nb,b", [(1, 1), (3, 5), (1, 16), (2, 16), (11, 3), (4, 16), (5, 13),
-                                  (4, 24), (8, 16), (25, 8)])
+                                  (4, 24), (8, 16), (25, 8), (70, 2)])
 @pytest.mark.parametrize("kind", ["symmetric", "general", "one bit"])
 def test_dense_products_at_tile_edges(nb, b, kind):
     from paper_2003_03868_amd import bsm
