@@ -731,7 +731,7 @@ def main():
                 and args.eps == 1e-6 and args.table == "exhaustive" and args.screen == 0.0)
             else None,
             "traffic_unit": "HBM bytes per launch (rocprofv3 FETCH_SIZE x2 + WRITE_SIZE, "
-                            "profiles/k_smm_f64_quad_sign23.md)",
+                            "profiles/k_smm_f64_tile_sign23.md)",
             "smm_ms_per_step": smm_ms / args.steps,
         },
         "cpu_baseline": cpu,
