@@ -530,7 +530,9 @@ int multiply(double alpha, Mat &A, Mat &B, double beta, Mat &C, double eps, int 
             };
             QuadSymArgs qa{};
             qa.r0 = r0; qa.r1 = r1; qa.nbcols = B.nbcols; qa.gr = GR; qa.gc = GC;
-            qa.nseg = quad_ksegments(A.nbcols);
+            // one workgroup per row group and segment, fewer than 2^32 threads
+            qa.nseg = static_cast<int32_t>(std::min<int64_t>(
+                quad_ksegments(A.nbcols), std::max<int64_t>(1, kQuadListGroups / std::max<int64_t>(1, npairs))));
             qa.kseg = (A.nbcols + qa.nseg - 1) / qa.nseg;
             if (qa.kseg < 1) qa.kseg = 1;
             qa.a_row_ptr = A.row_ptr; qa.a_col_idx = A.col_idx;

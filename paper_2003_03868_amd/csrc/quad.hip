@@ -368,7 +368,7 @@ int quad_stack(const QuadSymArgs &q, bool fill, hipStream_t s) {
     const size_t lds = sizeof(uint32_t) * 2 * quad_nwq(q) +
                        sizeof(int32_t) * kQuadWindow * (fill ? 2 : 1);
     const int64_t nblk = ngroups * q.nseg;
-    if (nblk > (1ll << 31) - 1) { set_error("too many row groups in one chunk"); return BSM_EINVAL; }
+    if (nblk > kQuadListGroups) { set_error("too many row groups in one chunk"); return BSM_EINVAL; }
     const unsigned g = static_cast<unsigned>(nblk);
     if (q.map) {
         if (q.gr != 2 || q.gc != 2) { set_error("internal: mixed groups are 2 x 2"); return BSM_EINVAL; }

@@ -77,6 +77,7 @@ struct SmmArgs {
                                 // B(col 0..GC-1) block indices, -1 where absent
     const int64_t *q_order;     // group of work item i (NULL: identity)
     int32_t q_gr, q_gc;         // group shape
+    int64_t q_first, q_count;   // groups of this launch (smm_group.h)
     int32_t nbr, nbc;           // block rows and columns of C
     const int32_t *q_pm;        // product mask per entry (bit GC r + c), NULL: all products
 };
@@ -140,8 +141,8 @@ bool smm_quad_available(int m, int n, int k);
 void quad_shape(int m, double reuse, int *gr, int *gc);
 int launch_quad(const SmmArgs &a, hipStream_t s);
 bool smm_tile_available(int m);   // 4 x 4 groups of uniform size m (smm_tile.hip)
-int launch_tile(const SmmArgs &a, unsigned grid, hipStream_t s);
-int launch_mtile(const SmmArgs &a, unsigned grid, hipStream_t s);  // 4 x 4 groups of mixed sizes (smm_mtile.hip)
+int launch_tile(const SmmArgs &a, hipStream_t s);
+int launch_mtile(const SmmArgs &a, hipStream_t s);  // 4 x 4 groups of mixed sizes (smm_mtile.hip)
 // Mixed-size groups (smm_mquad.hip): one persistent launch over a.n_quads
 // groups built with paired rows and columns (a.counter: work counter).
 int launch_mquad(const SmmArgs &a, hipStream_t s);
@@ -163,6 +164,6 @@ int smm_launch_lowp(const SmmArgs &a, hipStream_t s);
 int64_t lowp_image_words(int64_t nblocks, int size, int prec);
 int pack_lowp_image(const double *v, int64_t nblocks, int size, int prec, bool b_side, uint32_t *out,
                     hipStream_t s);
-int launch_lowp_tile(const SmmArgs &a, unsigned grid, hipStream_t s);
+int launch_lowp_tile(const SmmArgs &a, hipStream_t s);
 
 }  // namespace bsm

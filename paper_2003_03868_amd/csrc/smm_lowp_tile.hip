@@ -21,7 +21,7 @@
 // parts); 4 x 2 groups of eight waves, three per CU, 20.5 (two parts 14.1).
 #include "bf16_split.h"
 #include "lds_dma.h"
-#include "smm.h"
+#include "smm_group.h"
 
 namespace bsm {
 
@@ -113,10 +113,8 @@ k_lowp_tile(SmmArgs a) {
     const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(
         (__attribute__((address_space(3))) char *)lds));
     constexpr uint32_t zero0 = 2 * STAGE + TAIL;
-    const int64_t per = (a.n_quads + kXcds - 1) / kXcds;
-    if (static_cast<int64_t>(blockIdx.x / kXcds) >= per) return;
-    const int64_t it = static_cast<int64_t>(blockIdx.x % kXcds) * per + blockIdx.x / kXcds;
-    if (it >= a.n_quads) return;
+    const int64_t it = group_item(a);
+    if (it < 0) return;
     const int64_t item = a.q_order ? a.q_order[it] : it;
     const int lane = threadIdx.x % kWave;
     const int wv = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x / kWave));
@@ -368,20 +366,19 @@ int pack_lowp_image(const double *v, int64_t nblocks, int size, int prec, bool b
     return BSM_OK;
 }
 
-int launch_lowp_tile(const SmmArgs &a, unsigned grid, hipStream_t s) {
+int launch_lowp_tile(const SmmArgs &a, hipStream_t s) {
     switch (a.uni_m) {
 #define BSM_LT(S)                                                                                      \
         case S:                                                                                        \
-            if (a.prec == BSM_FP32) BSM_LAUNCH((k_lowp_tile<S, 0, lowp_eps(S)>), grid, 512, 0, s)(a); \
-            else if (a.prec == BSM_SPLIT_BF16) BSM_LAUNCH((k_lowp_tile<S, 2, lowp_eps(S)>), grid, 512, 0, s)(a); \
-            else BSM_LAUNCH((k_lowp_tile<S, 3, lowp_eps(S)>), grid, 512, 0, s)(a);   \
-            break;
+            return launch_groups(a, 512, [&](const SmmArgs &b, unsigned grid) {                        \
+                if (b.prec == BSM_FP32) BSM_LAUNCH((k_lowp_tile<S, 0, lowp_eps(S)>), grid, 512, 0, s)(b); \
+                else if (b.prec == BSM_SPLIT_BF16) BSM_LAUNCH((k_lowp_tile<S, 2, lowp_eps(S)>), grid, 512, 0, s)(b); \
+                else BSM_LAUNCH((k_lowp_tile<S, 3, lowp_eps(S)>), grid, 512, 0, s)(b);                 \
+            });
         BSM_LT_SIZES(BSM_LT)
 #undef BSM_LT
         default: set_error("no reduced-precision tile kernel for block size %d", a.uni_m); return BSM_EINVAL;
     }
-    BSM_HIP(hipGetLastError());
-    return BSM_OK;
 }
 
 }  // namespace bsm

@@ -24,19 +24,13 @@
 // starts a group.  Tried: sixteen waves of one C block, one group per CU and
 // twice the stage: 11 .. 8% slower.
 #include "lds_dma.h"
-#include "smm.h"
+#include "smm_group.h"
 
 namespace bsm {
 
 namespace {
 
 typedef __attribute__((address_space(3))) double lds_double;
-
-__device__ inline int64_t tile_item(int64_t n_items) {
-    const int64_t per = (n_items + kXcds - 1) / kXcds;
-    if (static_cast<int64_t>(blockIdx.x / kXcds) >= per) return n_items;
-    return static_cast<int64_t>(blockIdx.x % kXcds) * per + blockIdx.x / kXcds;
-}
 
 __device__ inline double t_wave_sum(double v) {
     for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
@@ -200,9 +194,8 @@ k_smm_f64_mtile(SmmArgs a) {
     __shared__ int wsum[8];
     const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(
         (__attribute__((address_space(3))) char *)lds));
-    const int64_t n_items = a.n_quads_dev ? *a.n_quads_dev : a.n_quads;
-    const int64_t it = tile_item(n_items);
-    if (it >= n_items) return;
+    const int64_t it = group_item(a);
+    if (it < 0) return;
     const int64_t item = a.q_order ? a.q_order[it] : it;
     const int lane = threadIdx.x % kWave;
     const int wv = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x / kWave));
@@ -347,10 +340,10 @@ k_smm_f64_mtile(SmmArgs a) {
 
 }  // namespace
 
-int launch_mtile(const SmmArgs &a, unsigned grid, hipStream_t s) {
-    BSM_LAUNCH((k_smm_f64_mtile<34816>), grid, 512, 0, s)(a);
-    BSM_HIP(hipGetLastError());
-    return BSM_OK;
+int launch_mtile(const SmmArgs &a, hipStream_t s) {
+    return launch_groups(a, 512, [&](const SmmArgs &b, unsigned grid) {
+        BSM_LAUNCH((k_smm_f64_mtile<34816>), grid, 512, 0, s)(b);
+    });
 }
 
 }  // namespace bsm

@@ -423,6 +423,12 @@ void quad_shape(int m, double reuse, int *gr, int *gc) {
 
 int launch_quad(const SmmArgs &a, hipStream_t s) {
     if (a.n_quads <= 0) return BSM_OK;
+    if (a.prec != BSM_FP64) return launch_lowp_tile(a, s);
+    if (!(a.uni_m && a.uni_n && a.uni_k)) {
+        if (a.q_gr != 4 || a.q_gc != 4) { set_error("internal: mixed-size groups are 4 x 4"); return BSM_EINVAL; }
+        return launch_mtile(a, s);
+    }
+    if (a.q_gr == 4 && a.q_gc == 4) return launch_tile(a, s);
     const int64_t per = (a.n_quads + kXcds - 1) / kXcds;
     const int64_t grid = per * kXcds;
     if (grid > (1ll << 31) - 1) {
@@ -430,7 +436,6 @@ int launch_quad(const SmmArgs &a, hipStream_t s) {
         return BSM_EINVAL;
     }
     const unsigned g = static_cast<unsigned>(grid);
-    if (a.prec != BSM_FP64) return launch_lowp_tile(a, g, s);
     const int w = quad_waves(), eps = quad_stage();
     if (a.q_pm) {
         // product masks (norm screening): quads with four waves (sizes 5, 6: one)
@@ -452,11 +457,6 @@ int launch_quad(const SmmArgs &a, hipStream_t s) {
         BSM_HIP(hipGetLastError());
         return BSM_OK;
     }
-    if (!(a.uni_m && a.uni_n && a.uni_k)) {
-        if (a.q_gr != 4 || a.q_gc != 4) { set_error("internal: mixed-size groups are 4 x 4"); return BSM_EINVAL; }
-        return launch_mtile(a, g, s);
-    }
-    if (a.q_gr == 4 && a.q_gc == 4) return launch_tile(a, g, s);
     if (a.q_gr != 2 || a.q_gc != 2) {
         set_error("internal: no %d x %d group kernel for block size %d", a.q_gr, a.q_gc, a.uni_m);
         return BSM_EINVAL;

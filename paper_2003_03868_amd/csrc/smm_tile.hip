@@ -31,7 +31,7 @@
 // it waits at its barrier), eight waves of 2 x 1 C blocks (322 -> 330 ms),
 // groups ordered in square tiles (346 -> 354 .. 363 ms).
 #include "lds_dma.h"
-#include "smm.h"
+#include "smm_group.h"
 
 namespace bsm {
 
@@ -49,14 +49,6 @@ struct TShape {
     // padded reads past the last block: A rows up to 8 H, B rows up to 4 KS
     static constexpr int TAIL = (8 * H * S - B2 + 64) * 8;
 };
-
-// Work item of this workgroup: the items form kXcds contiguous ranges, one
-// per XCD (as in the quad kernel); n_items for a workgroup past its range.
-__device__ inline int64_t tile_item(int64_t n_items) {
-    const int64_t per = (n_items + kXcds - 1) / kXcds;
-    if (static_cast<int64_t>(blockIdx.x / kXcds) >= per) return n_items;
-    return static_cast<int64_t>(blockIdx.x % kXcds) * per + blockIdx.x / kXcds;
-}
 
 __device__ inline double t_wave_sum(double v) {
     for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
@@ -115,9 +107,8 @@ k_smm_f64_tile(SmmArgs a) {
     __shared__ __align__(16) char lds[2 * STAGE + T::TAIL];
     const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(
         (__attribute__((address_space(3))) char *)lds));
-    const int64_t n_items = a.n_quads_dev ? *a.n_quads_dev : a.n_quads;
-    const int64_t it = tile_item(n_items);
-    if (it >= n_items) return;
+    const int64_t it = group_item(a);
+    if (it < 0) return;
     const int64_t item = a.q_order ? a.q_order[it] : it;
     const int lane = threadIdx.x % kWave;
     const int wv = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x / kWave));
@@ -244,10 +235,13 @@ constexpr int tile_eps(int s) { return s <= 12 ? 4 : s <= 17 ? 2 : 1; }
 
 bool smm_tile_available(int m) { return m >= 4 && m <= kMaxBlock; }
 
-int launch_tile(const SmmArgs &a, unsigned grid, hipStream_t s) {
+int launch_tile(const SmmArgs &a, hipStream_t s) {
     switch (a.uni_m) {
 #define BSM_TILE(S) \
-        case S: BSM_LAUNCH((k_smm_f64_tile<S, tile_eps(S), (S <= 24 ? 8 : 4)>), grid, 1024, 0, s)(a); break;
+        case S:                                                                                \
+            return launch_groups(a, 1024, [&](const SmmArgs &b, unsigned grid) {               \
+                BSM_LAUNCH((k_smm_f64_tile<S, tile_eps(S), (S <= 24 ? 8 : 4)>), grid, 1024, 0, s)(b); \
+            });
         BSM_TILE(4) BSM_TILE(5) BSM_TILE(6) BSM_TILE(7) BSM_TILE(8) BSM_TILE(9) BSM_TILE(10)
         BSM_TILE(11) BSM_TILE(12) BSM_TILE(13) BSM_TILE(14) BSM_TILE(15) BSM_TILE(16) BSM_TILE(17)
         BSM_TILE(18) BSM_TILE(19) BSM_TILE(20) BSM_TILE(21) BSM_TILE(22) BSM_TILE(23) BSM_TILE(24)
@@ -256,8 +250,6 @@ int launch_tile(const SmmArgs &a, unsigned grid, hipStream_t s) {
 #undef BSM_TILE
         default: set_error("no 4 x 4 tile kernel for block size %d", a.uni_m); return BSM_EINVAL;
     }
-    BSM_HIP(hipGetLastError());
-    return BSM_OK;
 }
 
 }  // namespace bsm

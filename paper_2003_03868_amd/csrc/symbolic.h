@@ -99,6 +99,8 @@ struct MixedPairs {
 };
 void mixed_pairs(const std::vector<int32_t> &rbs, const std::vector<int32_t> &cbs, MixedPairs *mp);
 
+// Workgroups of 256 threads that one launch of the list builders may have.
+constexpr int64_t kQuadListGroups = (int64_t{1} << 32) / 256 - 1;
 // k segments of the group lists' walk for nbk block columns of A.
 int32_t quad_ksegments(int32_t nbk);
 int quad_pairs(const QuadSymArgs &q, int64_t *cnt, hipStream_t s);
