@@ -47,12 +47,10 @@ struct LImage {
     static constexpr int BYTES = PIECES * 16;
 };
 
-// One workgroup per block: its image from the FP64 values.
+// The block's image from its FP64 values (one workgroup).
 template <int S, int T, bool B>
-__global__ __launch_bounds__(64) void k_pack_image(const double *v, uint32_t *out) {
+__device__ inline void pack_image(const double *src, char *dst) {
     using I = LImage<S, T>;
-    const double *src = v + static_cast<int64_t>(blockIdx.x) * (S * S);
-    char *dst = reinterpret_cast<char *>(out) + static_cast<int64_t>(blockIdx.x) * I::BYTES;
     if constexpr (T == 0) {
         for (int u = threadIdx.x; u < I::BYTES / 4; u += 64) {
             const int k = u / S, i = u % S;
@@ -76,6 +74,14 @@ __global__ __launch_bounds__(64) void k_pack_image(const double *v, uint32_t *ou
             for (int q = 0; q < T; ++q) *reinterpret_cast<us8 *>(dst + q * I::PART + u * 16) = part[q];
         }
     }
+}
+
+// One workgroup per block, or in turn where the blocks are more than a launch
+// may have workgroups.
+template <int S, int T, bool B>
+__global__ __launch_bounds__(64) void k_pack_image(const double *v, int64_t n, uint32_t *out) {
+    for (int64_t t = blockIdx.x; t < n; t += gridDim.x)
+        pack_image<S, T, B>(v + t * (S * S), reinterpret_cast<char *>(out) + t * LImage<S, T>::BYTES);
 }
 
 __device__ inline double l_wave_sum(double v) {
@@ -325,8 +331,9 @@ int64_t image_words(int prec) {
 
 template <int S, int T>
 void pack_side(const double *v, int64_t n, bool b_side, uint32_t *out, hipStream_t s) {
-    if (b_side) k_pack_image<S, T, true><<<static_cast<unsigned>(n), 64, 0, s>>>(v, out);
-    else k_pack_image<S, T, false><<<static_cast<unsigned>(n), 64, 0, s>>>(v, out);
+    const unsigned grid = static_cast<unsigned>(std::min<int64_t>(n, (int64_t{1} << 32) / 64 - 1));
+    if (b_side) k_pack_image<S, T, true><<<grid, 64, 0, s>>>(v, n, out);
+    else k_pack_image<S, T, false><<<grid, 64, 0, s>>>(v, n, out);
 }
 
 }  // namespace

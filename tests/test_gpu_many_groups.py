@@ -67,3 +67,32 @@ def test_reduced_precision(monkeypatch):
     monkeypatch.setenv("BSM_LOWP_QUAD", "1")
     name, same = _outer(257, 5, 5, 1)
     assert "k_lowp_tile" in name and same
+
+
+def test_reduced_precision_many_operand_blocks(monkeypatch):
+    """An operand of 2^26 + 65,536 blocks of 5: more than one launch may have
+    workgroups of 64 to pack them."""
+    import torch
+    from paper_2003_03868_amd import bsm
+    monkeypatch.setenv("BSM_LOWP_QUAD", "1")
+    nb, nk, s = 8200, 8192, 5
+    g = torch.Generator(device="cuda").manual_seed(5)
+    a = torch.empty(nb, nk, s, s, dtype=torch.float64, device="cuda").random_(0, 8, generator=g)
+    b = torch.empty(2, s, s, dtype=torch.float64, device="cuda").random_(0, 8, generator=g)
+    rows = [3, nk - 1]                         # B's blocks, in its only block column
+    size = lambda n: np.full(n, s, dtype=np.int32)
+    a_ptr = torch.arange(nb + 1, device="cuda") * nk
+    a_col = torch.arange(nk, dtype=torch.int32, device="cuda").repeat(nb)
+    b_ptr = torch.zeros(nk + 1, dtype=torch.int64, device="cuda")
+    b_ptr[rows[0] + 1:] = 1
+    b_ptr[nk] = 2
+    b_col = torch.zeros(2, dtype=torch.int32, device="cuda")
+    torch.cuda.synchronize()
+    ma = bsm.Matrix(bsm.bsm_create(nb, nk, size(nb), size(nk), nb * nk, a_ptr, a_col, a, 1), size(nb), size(nk))
+    mb = bsm.Matrix(bsm.bsm_create(nk, 1, size(nk), size(1), 2, b_ptr, b_col, b, 1), size(nk), size(1))
+    mc = bsm.Matrix.empty_like(size(nb), size(1))
+    bsm.bsm_multiply(1.0, ma.handle, mb.handle, 0.0, mc.handle, 0.0, 0, bsm.FP32)
+    assert "k_lowp_tile" in bsm.bsm_last_smm_kernel()
+    got = torch.from_numpy(mc.export()[2]).cuda()
+    want = sum(a[:, r].reshape(-1, s) @ b[q] for q, r in enumerate(rows))
+    assert torch.equal(got, want.reshape(-1))
