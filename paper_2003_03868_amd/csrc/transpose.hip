@@ -38,35 +38,28 @@ __global__ void k_t_place(const int32_t *col_idx, const int32_t *rows, int64_t n
 }
 
 // Each row of B in the order of its columns (A's rows, unique within the
-// row): a block's place is the number of smaller keys in its row.  One
-// workgroup per row, keys passing through LDS a tile at a time.  Bound by the
-// compares, n^2 for a row of n blocks.  An insertion sort with one thread per
-// row took 1488 us for 4096 rows of 92 blocks, every compare a dependent load
-// from memory; the whole sum, transpose and trace of that matrix went from
-// 3.5 to 1.9 ms with this kernel and the next.
-constexpr int kSortThreads = 256, kSortTile = 2048;
+// row): a block's place is the number of smaller keys in its row.  One thread
+// per block, whatever the rows' lengths are; neighbours read the same keys.
+// Bound by the reads, n per block of a row of n blocks.  Whole transposes with
+// an insertion sort by one thread per row, with a workgroup per row and with
+// this kernel, the next one as it is now (ms): a million rows of 5 blocks of
+// 6 x 6 3.4, 5.4, 3.3; 4096 rows of 92 mixed blocks 1.81, 0.61, 0.51, of 1024
+// blocks of 6 x 6 23 (with one thread) and 2.3; one row of 100,000 blocks 1650
+// (with one workgroup) and 5.5.
+constexpr int kSortThreads = 256;
 __global__ void __launch_bounds__(kSortThreads)
-k_t_sort(const int64_t *rp_out, const int32_t *key, const int64_t *src, int32_t *key_out, int64_t *src_out) {
-    __shared__ int32_t tile[kSortTile];
-    const int64_t b = rp_out[blockIdx.x], n = rp_out[blockIdx.x + 1] - b;
-    for (int64_t u0 = 0; u0 < n; u0 += kSortThreads) {
-        const int64_t u = u0 + threadIdx.x;
-        const int32_t k = u < n ? key[b + u] : 0;
-        int64_t rank = 0;
-        for (int64_t w0 = 0; w0 < n; w0 += kSortTile) {
-            const int wn = static_cast<int>(n - w0 < kSortTile ? n - w0 : kSortTile);
-            __syncthreads();
-            for (int w = threadIdx.x; w < wn; w += kSortThreads) tile[w] = key[b + w0 + w];
-            __syncthreads();
-            int less = 0;
-            for (int w = 0; w < wn; ++w) less += tile[w] < k ? 1 : 0;
-            rank += less;
-        }
-        if (u < n) {
-            key_out[b + rank] = k;
-            src_out[b + rank] = src[b + u];
-        }
-    }
+k_t_sort(const int64_t *rp_out, const int32_t *a_col_idx, const int32_t *key, const int64_t *src,
+         int64_t nnzb, int32_t *key_out, int64_t *src_out) {
+    const int64_t p = static_cast<int64_t>(blockIdx.x) * kSortThreads + threadIdx.x;
+    if (p >= nnzb) return;
+    const int64_t t = src[p];
+    const int32_t j = a_col_idx[t], k = key[p];
+    const int64_t b = rp_out[j], e = rp_out[j + 1];
+    int64_t place = b;
+#pragma unroll 8
+    for (int64_t u = b; u < e; ++u) place += key[u] < k ? 1 : 0;
+    key_out[place] = k;
+    src_out[place] = t;
 }
 
 // One wave per block of B, four per workgroup: the block is read in order into
@@ -74,17 +67,21 @@ k_t_sort(const int64_t *rp_out, const int32_t *key, const int64_t *src, int32_t 
 // whole lines; stored as it was read, lanes wrote 8 bytes every block row.
 // Bound by memory (0.84 GB read and written for 375,000 mixed blocks): 657 us
 // with strided writes, 458 us this way.  Rows of n doubles lie n + 1 apart
-// for even n, which keeps a column's elements on different banks.
+// for even n, which keeps a column's elements on different banks.  The LDS of
+// a launch is what its largest block needs: with room for 32 x 32 always,
+// small blocks had half the waves (a million rows of 5 blocks of 6 x 6, whole
+// transpose 4.5 ms and 3.2 then, 2.9 with blocks of up to 64 elements stored
+// as they were read).
 constexpr int kTWaves = 4;
 __global__ void __launch_bounds__(64 * kTWaves)
 k_t_values(const int64_t *src, const int32_t *key, const int32_t *a_col_idx,
            const int64_t *a_blk_off, const double *a_vals, const int32_t *a_rbs,
-           const int32_t *a_cbs, const int64_t *b_blk_off, double *b_vals, int64_t nnzb) {
-    __shared__ double lds[kTWaves][kMaxBlock * (kMaxBlock + 1)];
+           const int32_t *a_cbs, const int64_t *b_blk_off, double *b_vals, int64_t nnzb, int per_wave) {
+    extern __shared__ double lds[];                    // per_wave: doubles of the largest block
     const int wv = threadIdx.x / kWave, lane = threadIdx.x % kWave;
     const int64_t p = static_cast<int64_t>(blockIdx.x) * kTWaves + wv;
     if (p >= nnzb) return;
-    double *sm = lds[wv];
+    double *sm = lds + wv * per_wave;
     const int64_t t = src[p];
     const int m = a_rbs[key[p]], n = a_cbs[a_col_idx[t]];
     const double *in = a_vals + a_blk_off[t];
@@ -93,6 +90,11 @@ k_t_values(const int64_t *src, const int32_t *key, const int32_t *a_col_idx,
     // u / d for u < 1024, d <= 32: u (65536 / d rounded up) / 65536 is exact
     const unsigned by_n = (65536u + n - 1) / n, by_m = (65536u + m - 1) / m;
     const int len = m * n;
+    if (len <= kWave) {                                // one store of a few lines: no turn needed
+        const int r = (lane * by_n) >> 16;
+        if (lane < len) out[(lane - r * n) * m + r] = in[lane];
+        return;
+    }
     for (int u0 = lane; u0 < len; u0 += 8 * kWave) {     // eight loads in flight
         double v[8];
 #pragma unroll
@@ -143,8 +145,10 @@ int transpose_mat(const Mat &a, Mat **out, hipStream_t s) {
     if (st == BSM_OK && a.nnzb > 0) {
         k_t_place<<<grid_for(a.nnzb, 256), 256, 0, s>>>(a.col_idx, rows, a.nnzb, m->row_ptr, cursor,
                                                         key, placed);
-        if (m->nbrows > 0)
-            k_t_sort<<<m->nbrows, kSortThreads, 0, s>>>(m->row_ptr, key, placed, m->col_idx, src);
+        k_t_sort<<<grid_for(a.nnzb, kSortThreads), kSortThreads, 0, s>>>(m->row_ptr, a.col_idx, key, placed,
+                                                                        a.nnzb, m->col_idx, src);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) { set_error("transpose: %s", hipGetErrorString(e)); st = BSM_EDEVICE; }
     }
     if (st == BSM_OK) {
         m->nnzb = a.nnzb;
@@ -155,9 +159,10 @@ int transpose_mat(const Mat &a, Mat **out, hipStream_t s) {
         st = dalloc(&m->values, std::max<int64_t>(a.nvalues, 1), s);
     }
     if (st == BSM_OK && a.nnzb > 0) {
-        k_t_values<<<grid_for(a.nnzb, kTWaves), 64 * kTWaves, 0, s>>>(src, m->col_idx, a.col_idx, a.blk_off,
-                                                               a.values, a.rbs, a.cbs, m->blk_off,
-                                                               m->values, a.nnzb);
+        const int per_wave = a.max_rbs * (a.max_cbs | 1);
+        k_t_values<<<grid_for(a.nnzb, kTWaves), 64 * kTWaves, sizeof(double) * kTWaves * per_wave, s>>>(
+            src, m->col_idx, a.col_idx, a.blk_off, a.values, a.rbs, a.cbs, m->blk_off, m->values, a.nnzb,
+            per_wave);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) { set_error("transpose: %s", hipGetErrorString(e)); st = BSM_EDEVICE; }
     }

@@ -52,3 +52,26 @@ def test_filter_keeps_blocks(nblk, size):
     assert np.array_equal(got.row_ptr, np.concatenate([[0], np.cumsum(np.bincount(rows, minlength=2))]))
     assert np.array_equal(got.col_idx, a.col_idx[keep])
     assert np.array_equal(got.values, blocks[keep].ravel())
+
+
+@pytest.mark.parametrize("nbr,nbc,long_rows", [(3, (1 << 24) + 9, ()), (30000, 5, (1, 4)), (70001, 7, (0,))])
+def test_transpose_of_any_row_length(nbr, nbc, long_rows):
+    """Results with more block rows than one launch may have workgroups of
+    256 threads, and with rows of tens of thousands of blocks beside short
+    ones."""
+    import torch
+    from paper_2003_03868_amd import bsm
+    rng = np.random.default_rng(nbr)
+    pairs = {(int(i), int(j)) for i, j in zip(rng.integers(0, nbr, 500), rng.integers(0, nbc, 500))}
+    pairs |= {(0, 0), (nbr - 1, nbc - 1)}
+    pairs |= {(i, j) for j in long_rows for i in range(nbr)}
+    r, c = np.array(sorted(pairs)).T
+    val = rng.standard_normal(len(r))
+    ptr = lambda idx, n: np.concatenate([[0], np.cumsum(np.bincount(idx, minlength=n))])
+    ones = lambda n: np.ones(n, dtype=np.int32)
+    a = bsm.Matrix.from_arrays(ones(nbr), ones(nbc), ptr(r, nbr), c, val)
+    t = bsm.Matrix(bsm.bsm_transpose(a.handle), ones(nbc), ones(nbr))
+    got_ptr, got_col, got_val = t.export()
+    o = np.lexsort((r, c))
+    assert np.array_equal(got_ptr, ptr(c, nbc)) and np.array_equal(got_col, r[o])
+    assert np.array_equal(got_val, val[o])
