@@ -211,31 +211,42 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
     }
 }
 
-// Clears `flag` (nonzero beforehand) unless H equals its transpose: every
-// stored block (i, j) has a stored (j, i) with the mirrored values.  One
-// workgroup per block row, a wave per block; NaN is unequal to itself.
+// Workgroups of the kernels over block rows, which take rows in turn.
+constexpr int kRowGroups = 4096;
+
+// Adds to *mirrored (zero beforehand) the number of stored blocks (i, j) with a
+// stored (j, i) of the mirrored values: H is its own transpose where that is
+// all of them.  One workgroup per block row at a time, a wave per block; NaN
+// is unequal to itself.
 __global__ __launch_bounds__(256) void k_sub_symmetric(const int64_t *row_ptr, const int32_t *col_idx,
                                                        const int64_t *blk_off, const double *vals,
-                                                       const int32_t *rbs, int32_t *flag) {
-    const int i = blockIdx.x;
-    const int lane = threadIdx.x & 63;
-    const int bi = rbs[i];
-    for (int64_t t = row_ptr[i] + (threadIdx.x >> 6); t < row_ptr[i + 1]; t += 4) {
-        const int j = col_idx[t];
-        int64_t lo = row_ptr[j], hi = row_ptr[j + 1];
-        const int64_t end = hi;
-        while (lo < hi) {
-            const int64_t mid = (lo + hi) >> 1;
-            if (col_idx[mid] < i) lo = mid + 1; else hi = mid;
+                                                       const int32_t *rbs, int32_t nb,
+                                                       unsigned long long *mirrored) {
+    __shared__ unsigned long long cnt[4];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    unsigned long long n = 0;
+    for (int i = blockIdx.x; i < nb; i += gridDim.x) {
+        const int bi = rbs[i];
+        for (int64_t t = row_ptr[i] + w; t < row_ptr[i + 1]; t += 4) {
+            const int j = col_idx[t];
+            int64_t lo = row_ptr[j], hi = row_ptr[j + 1];
+            const int64_t end = hi;
+            while (lo < hi) {
+                const int64_t mid = (lo + hi) >> 1;
+                if (col_idx[mid] < i) lo = mid + 1; else hi = mid;
+            }
+            bool same = lo < end && col_idx[lo] == i;
+            if (same) {
+                const int bj = rbs[j];
+                const double *a = vals + blk_off[t], *b = vals + blk_off[lo];
+                for (int u = lane; u < bi * bj; u += 64) same = same && a[u] == b[u % bj * bi + u / bj];
+            }
+            if (__all(same)) ++n;
         }
-        bool same = lo < end && col_idx[lo] == i;
-        if (same) {
-            const int bj = rbs[j];
-            const double *a = vals + blk_off[t], *b = vals + blk_off[lo];
-            for (int u = lane; u < bi * bj; u += 64) same = same && a[u] == b[u % bj * bi + u / bj];
-        }
-        if (!same) *flag = 0;
     }
+    if (lane == 0) cnt[w] = n;
+    __syncthreads();
+    if (threadIdx.x == 0) atomicAdd(mirrored, cnt[0] + cnt[1] + cnt[2] + cnt[3]);
 }
 
 // r = ||Y - I||_F / n per active submatrix from its tiles' partial sums
@@ -250,20 +261,23 @@ __global__ void k_sub_resid(const double *partial, const int32_t *act_sub, const
 }
 
 // Row sums of |H - mu I| of every stored block: those of block t at
-// sums[blk_off[t]], one per row.  One workgroup per block row, a thread per
-// row of a block.
+// sums[blk_off[t]], one per row.  One workgroup per block row at a time, a
+// thread per row of a block.
 __global__ __launch_bounds__(256) void k_sub_block_sums(const int64_t *row_ptr, const int32_t *col_idx,
                                                         const int64_t *blk_off, const double *vals,
-                                                        const int32_t *rbs, double mu, double *sums) {
-    const int i = blockIdx.x, bi = rbs[i];
-    const int64_t t0 = row_ptr[i], n = (row_ptr[i + 1] - t0) * bi;
-    for (int64_t q = threadIdx.x; q < n; q += blockDim.x) {
-        const int64_t t = t0 + q / bi;
-        const int u = static_cast<int>(q % bi), j = col_idx[t], bj = rbs[j];
-        const double *h = vals + blk_off[t] + static_cast<int64_t>(u) * bj;
-        double s = 0.0;
-        for (int v = 0; v < bj; ++v) s += fabs(h[v] - ((j == i && u == v) ? mu : 0.0));
-        sums[blk_off[t] + u] = s;
+                                                        const int32_t *rbs, int32_t nb, double mu,
+                                                        double *sums) {
+    for (int i = blockIdx.x; i < nb; i += gridDim.x) {
+        const int bi = rbs[i];
+        const int64_t t0 = row_ptr[i], n = (row_ptr[i + 1] - t0) * bi;
+        for (int64_t q = threadIdx.x; q < n; q += blockDim.x) {
+            const int64_t t = t0 + q / bi;
+            const int u = static_cast<int>(q % bi), j = col_idx[t], bj = rbs[j];
+            const double *h = vals + blk_off[t] + static_cast<int64_t>(u) * bj;
+            double s = 0.0;
+            for (int v = 0; v < bj; ++v) s += fabs(h[v] - ((j == i && u == v) ? mu : 0.0));
+            sums[blk_off[t] + u] = s;
+        }
     }
 }
 
@@ -416,18 +430,21 @@ int submatrix_density(Mat &H, double mu, const bsm_sign_opts &o, Mat **p_out, bs
         BSM_HIP(hipMemcpyAsync(ci.data(), H.col_idx, sizeof(int32_t) * H.nnzb, hipMemcpyDeviceToHost, s));
     // whether H is its own transpose: half of every product is then the
     // mirror image of the other
-    int32_t symmetric = 1;
-    const std::vector<int32_t> yes(1, 1);
+    unsigned long long mirrored = 0;
+    const std::vector<unsigned long long> none(1, 0);
     if (nb > 0) {
-        int32_t *d_flag = nullptr;
-        BSM_TRY(upload(&d_flag, yes, s));
-        hipLaunchKernelGGL(k_sub_symmetric, dim3(nb), dim3(256), 0, s, H.row_ptr, H.col_idx,
-                           H.blk_off, H.values, H.rbs, d_flag);
-        const hipError_t e = hipMemcpyAsync(&symmetric, d_flag, sizeof(int32_t), hipMemcpyDeviceToHost, s);
-        dfree(d_flag, s);
+        unsigned long long *d_mirrored = nullptr;
+        BSM_TRY(upload(&d_mirrored, none, s));
+        hipLaunchKernelGGL(k_sub_symmetric, dim3(std::min(nb, kRowGroups)), dim3(256), 0, s, H.row_ptr,
+                           H.col_idx, H.blk_off, H.values, H.rbs, nb, d_mirrored);
+        hipError_t e = hipGetLastError();
+        if (e == hipSuccess)
+            e = hipMemcpyAsync(&mirrored, d_mirrored, sizeof(mirrored), hipMemcpyDeviceToHost, s);
+        dfree(d_mirrored, s);
         BSM_HIP(e);
     }
     BSM_HIP(hipStreamSynchronize(s));
+    const bool symmetric = mirrored == static_cast<unsigned long long>(H.nnzb);
     std::vector<int64_t> cp(nb + 1, 0);
     for (int64_t t = 0; t < H.nnzb; ++t) cp[ci[t] + 1]++;
     for (int j = 0; j < nb; ++j) cp[j + 1] += cp[j];
@@ -478,9 +495,11 @@ int submatrix_density(Mat &H, double mu, const bsm_sign_opts &o, Mat **p_out, bs
     std::vector<std::pair<hipEvent_t, hipEvent_t>> gev;
     double *d_sums = nullptr;        // row sums of |H - mu I| per block
     if (rc == BSM_OK) rc = dalloc(&d_sums, std::max<size_t>(H.nvalues, 1), s);
-    if (rc == BSM_OK && nb > 0)
-        hipLaunchKernelGGL(k_sub_block_sums, dim3(nb), dim3(256), 0, s, H.row_ptr, H.col_idx, H.blk_off,
-                           H.values, H.rbs, mu, d_sums);
+    if (rc == BSM_OK && nb > 0) {
+        hipLaunchKernelGGL(k_sub_block_sums, dim3(std::min(nb, kRowGroups)), dim3(256), 0, s, H.row_ptr,
+                           H.col_idx, H.blk_off, H.values, H.rbs, nb, mu, d_sums);
+        if (hipGetLastError() != hipSuccess) { set_error("submatrix: row sums failed"); rc = BSM_EDEVICE; }
+    }
     int64_t n_noconv = 0;            // submatrices left above tol (every batch still runs)
     int j0 = 0;
     while (rc == BSM_OK && j0 < nb) {
