@@ -260,13 +260,13 @@ __global__ void k_sub_resid(const double *partial, const int32_t *act_sub, const
     r[a] = sqrt(s) / static_cast<double>(ndim[act_sub[a]]);
 }
 
-// Row sums of |H - mu I| of every stored block: those of block t at
-// sums[blk_off[t]], one per row.  One workgroup per block row at a time, a
-// thread per row of a block.
+// Row sums of |H - mu I| of every stored block, one per row: those of block
+// row i follow sums[soff[i]], block after block.  One workgroup per block row
+// at a time, a thread per row of a block.
 __global__ __launch_bounds__(256) void k_sub_block_sums(const int64_t *row_ptr, const int32_t *col_idx,
                                                         const int64_t *blk_off, const double *vals,
                                                         const int32_t *rbs, int32_t nb, double mu,
-                                                        double *sums) {
+                                                        const int64_t *soff, double *sums) {
     for (int i = blockIdx.x; i < nb; i += gridDim.x) {
         const int bi = rbs[i];
         const int64_t t0 = row_ptr[i], n = (row_ptr[i + 1] - t0) * bi;
@@ -276,7 +276,7 @@ __global__ __launch_bounds__(256) void k_sub_block_sums(const int64_t *row_ptr, 
             const double *h = vals + blk_off[t] + static_cast<int64_t>(u) * bj;
             double s = 0.0;
             for (int v = 0; v < bj; ++v) s += fabs(h[v] - ((j == i && u == v) ? mu : 0.0));
-            sums[blk_off[t] + u] = s;
+            sums[soff[i] + q] = s;
         }
     }
 }
@@ -297,7 +297,7 @@ __device__ inline int64_t sub_find(const int32_t *col_idx, int64_t p0, int64_t p
 // Reading the assembled T_j instead took 0.51 ms for 1.9 GB, and scaling it
 // afterwards 0.81 ms; this way the gather writes scaled values (MI355X, 6192
 // submatrices of mean edge 189).
-__global__ void k_sub_norm(const int64_t *row_ptr, const int32_t *col_idx, const int64_t *blk_off,
+__global__ void k_sub_norm(const int64_t *row_ptr, const int32_t *col_idx, const int64_t *soff,
                            const double *sums, const int32_t *rbs, const int32_t *ent_row,
                            const int32_t *ent_sub, const int64_t *sub_ent0, double *scale,
                            int64_t nent) {
@@ -309,7 +309,7 @@ __global__ void k_sub_norm(const int64_t *row_ptr, const int32_t *col_idx, const
     double row = 0.0;
     for (int64_t f0 = sub_ent0[sub]; f0 < f1; f0 += 64) {
         const int64_t t = f0 + lane < f1 ? sub_find(col_idx, p0, p1, ent_row[f0 + lane]) : p1;
-        const double *b = t < p1 ? sums + blk_off[t] : nullptr;
+        const double *b = t < p1 ? sums + soff[i] + (t - p0) * bi : nullptr;
         for (int u = 0; u < bi; ++u) {
             double s = b ? b[u] : 0.0;
 #pragma unroll
@@ -494,10 +494,14 @@ int submatrix_density(Mat &H, double mu, const bsm_sign_opts &o, Mat **p_out, bs
     const size_t cap = batch_bytes_cap();
     std::vector<std::pair<hipEvent_t, hipEvent_t>> gev;
     double *d_sums = nullptr;        // row sums of |H - mu I| per block
-    if (rc == BSM_OK) rc = dalloc(&d_sums, std::max<size_t>(H.nvalues, 1), s);
+    int64_t *d_soff = nullptr;       // where those of a block row start
+    std::vector<int64_t> soff(nb + 1, 0);
+    for (int i = 0; i < nb; ++i) soff[i + 1] = soff[i] + (rp[i + 1] - rp[i]) * H.h_rbs[i];
+    if (rc == BSM_OK) rc = upload(&d_soff, soff, s);
+    if (rc == BSM_OK) rc = dalloc(&d_sums, std::max<int64_t>(soff[nb], 1), s);
     if (rc == BSM_OK && nb > 0) {
         hipLaunchKernelGGL(k_sub_block_sums, dim3(std::min(nb, kRowGroups)), dim3(256), 0, s, H.row_ptr,
-                           H.col_idx, H.blk_off, H.values, H.rbs, nb, mu, d_sums);
+                           H.col_idx, H.blk_off, H.values, H.rbs, nb, mu, d_soff, d_sums);
         if (hipGetLastError() != hipSuccess) { set_error("submatrix: row sums failed"); rc = BSM_EDEVICE; }
     }
     int64_t n_noconv = 0;            // submatrices left above tol (every batch still runs)
@@ -576,7 +580,7 @@ int submatrix_density(Mat &H, double mu, const bsm_sign_opts &o, Mat **p_out, bs
         }
         if (nent > 0)
             hipLaunchKernelGGL(k_sub_norm, dim3(static_cast<unsigned>(nent)), dim3(64), 0, s,
-                               H.row_ptr, H.col_idx, H.blk_off, d_sums, H.rbs, d_erow, d_esub,
+                               H.row_ptr, H.col_idx, d_soff, d_sums, H.rbs, d_erow, d_esub,
                                d_ent0, d_scale, nent);
         std::vector<double> scale(ns);
         if (hipMemcpyAsync(scale.data(), d_scale, sizeof(double) * ns, hipMemcpyDeviceToHost, s) !=
@@ -733,6 +737,7 @@ int submatrix_density(Mat &H, double mu, const bsm_sign_opts &o, Mat **p_out, bs
         j0 = j1;
     }
     dfree(d_sums, s);
+    dfree(d_soff, s);
     if (rc == BSM_OK) {
         const int r2 = filter_inplace(*P, o.eps_filter, o.norm, s);
         if (r2 != BSM_OK) rc = r2;
