@@ -109,6 +109,7 @@ struct MulSizes {
     int64_t nval_u = 0;      // C scalars before the filter
     int64_t nval = 0;        // C scalars after the filter
     int64_t n_products = 0;  // block products
+    double share = 1e300;    // products per entry of 4 x 4 groups (large: not counted)
     int64_t n_groups = 0;    // groups of C blocks of the group kernel, over all chunks
     int64_t n_entries = 0;   // their entries
     int gr = 0;              // rows of a group (0: as in the graphs that counted them)

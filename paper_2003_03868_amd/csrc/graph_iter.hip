@@ -309,7 +309,7 @@ bool graph_iter_ok(const Mat &X) {
         SmmParams tp;
         if (table_lookup(b, b, b, &tp) && tp.family != 3) return false;
         int gr = 2, gc = 2;
-        quad_shape(b, 0.0, &gr, &gc);
+        quad_shape(b, 0.0, 0.0, &gr, &gc);
         return gr == gc;
     }
     // mixed sizes: the paired groups in one persistent launch per multiply
@@ -579,7 +579,7 @@ int gi_enter(GraphIter *g, Mat &X, Mat &Y, const MulSizes &sq, const MulSizes &u
             g->nrg = g->mp.band_g0.back();
         } else {
             quad_shape(g->b, sq.nnzb_u ? static_cast<double>(sq.n_products) / static_cast<double>(sq.nnzb_u) : 0.0,
-                       &g->gr, &g->gc);
+                       sq.share, &g->gr, &g->gc);
             g->nrg = (static_cast<int64_t>(g->nbr) + g->gr - 1) / g->gr;
         }
         g->nseg = quad_ksegments(X.nbcols);

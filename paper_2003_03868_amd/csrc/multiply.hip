@@ -70,10 +70,47 @@ static double quad_min_reuse() {
 // 133; 32 18 74.0 and 73.4, 25 56.4 and 56.8, 92 242 and 250.  Few products
 // (7e5, reuse 18): 13 0.59 and 0.43, 23 0.96 and 0.74.  The sign iteration (`iter`)
 // has its multiplies from graphs where they run in groups, and keeps to them.
-static bool fp64_groups(int m, double reuse, int64_t nprod, bool iter) {
+// Those are neighbour lists along a Morton curve, about 5 products per 4 x 4
+// entry and more (`share`).  Where neighbouring rows and columns have little in
+// common, a group stages an operand for one or two products; one block and
+// groups then, ms: 23 share 1.1 69 and 113, 1.4 100 and 125, 1.9 48 and 48, 2.2
+// 613 and 500; 13 1.4 32 and 52, 2.0 15.7 and 19.3, 2.2 207 and 202; 5 2.2 56 and
+// 106, 4.6 25.6 and 27.8, 7.7 55 and 48; 26 2.2 854 and 1259, 4.6 386 and 395, 7.7
+// 790 and 685; 32 1.9 120 and 129, 4.6 658 and 668, 7.7 1402 and 1339.
+static bool fp64_groups(int m, double reuse, double share, int64_t nprod, bool iter) {
     if (iter || getenv("BSM_QUAD_MIN_REUSE")) return reuse >= quad_min_reuse();
     const double least = m == 23 ? 12.5 : (m == 13 || m == 32) ? 20.0 : 64.0;
-    return reuse >= least && nprod >= 1000000;
+    return reuse >= least && nprod >= 1000000 && share >= (m == 23 || m == 13 ? 2.1 : 5.0);
+}
+
+// Mixed sizes: 4 x 4 groups of consecutive block rows and columns.  Whole
+// multiplies with the one-block kernels and with groups, ms:
+//   any sizes ({4, 9, 13, 18, 22, 31}; the persistent kernel): 5e2 products
+//     0.23 and 0.28, 2e3 0.30 and 0.31, 2e4 0.55 and 0.46, 1.7e5 1.32 and
+//     0.67; 14.7 products per C block 18.5 and 7.9, 126 250 and 69.  The persistent
+//     kernel takes 12 ns per C block (its counter) or 1.9 per product, whichever
+//     is more, groups 16 ns each and 1.45 per entry ({1, 2, 3, 4}: 1.1 per product
+//     and 0.4 per entry).  With few products per entry, groups are many: a
+//     million C blocks of one product each, all in groups of their own, 13.2 and
+//     17.8; 1.3e6 products, 1.05 C blocks per group, 4.2 and 7.7; 4.2e6 products,
+//     3.6 C blocks per group, 45 and 24;
+//   {5, 13, 23, 26} (a launch per (m, n) class): 8.6e6 products, 15 per C block 5.9
+//     and 7.2; 4.8e7, 47 28.1 and 27.9; 2.7e8, 257 162 and 129, with 4.6 products
+//     per entry instead of 8.7 165 and 156, of 6.8e7 with 1.1 44 and 112.  Below
+//     50000 products per class the launches count, 0.4 ms against 0.25 for four
+//     sizes: 6e4 products 0.51 and 0.37, 2.3e5 0.67 and 0.54; with as many groups
+//     as C blocks, 6.5e4 0.50 and 0.93, 1.5e5 0.76 and 1.08; only 5 and 13 6e4 0.27
+//     and 0.32.
+// groups: at most so many; v: mean m n k of a product; classes: pairs of sizes.
+static bool mixed_groups(bool basis, double reuse, double share, double nprod, double n_c, double groups,
+                         double v, int classes) {
+    const double entries = nprod / share;
+    if (basis)
+        return (reuse >= 64.0 && share >= 4.5) ||
+               (nprod <= 50000.0 * classes && 16.0 * groups + (0.35 + v / 4500.0) * entries <
+                                                  12000.0 * (classes - 4) + (0.1 + v / 5000.0) * nprod);
+    return nprod >= 4000.0 && 16.0 * groups + (0.4 + v / 4000.0) * entries <
+                                  std::max(12.0 * n_c, (1.1 + v / 5000.0) * nprod);
 }
 
 // Groups of C blocks for reduced-precision products (uniform block size m,
@@ -90,12 +127,26 @@ static bool fp64_groups(int m, double reuse, int64_t nprod, bool iter) {
 //   FP32         743e3 5 0.43 and 0.52, 23 0.87 and 1.03, 32 1.29 and 1.20; reuse
 //     9.4, 5 1.45 and 1.81, 13 1.88 and 2.03; 18, 5 5.7 and 4.4, 13 7.6 and 6.1,
 //     23 21.3 and 23.3, 26 25.0 and 26.6; 47, 23 31.1 and 29.8, 26 36.3 and 33.6.
-static bool lowp_groups(int prec, int m, double reuse, int64_t nprod) {
+// With few products per entry (`share`; FP64 above), groups / one block:
+//   three parts  1.1 1.6 .. 2.3, 1.3 0.99 .. 1.28, 1.4 0.96 .. 1.09, 1.9 0.77 .. 0.95
+//     (32 the last of each), 4.6 0.47 .. 0.68;
+//   two parts    1.1 1.4 .. 2.4, 1.4 1.0 .. 1.6, 1.9 0.68 (32), 0.97 .. 1.19, 2.6 0.76
+//     (32), 1.06 (26), 4.6 0.42 .. 0.68;
+//   FP32         1.1 1.7 .. 2.5, 1.9 1.11 (32), 1.2 .. 1.6, 2.6 1.02 (32), 3.4 0.90
+//     (32), 1.23 (26), 4.6 0.71 (32, 13), 1.0 .. 1.06 (26, 23), 6.4 0.67 .. 0.97.
+// Small blocks with few products per C block gain from the groups' shorter
+// stacks all the same where the groups are full (`full`; 2.3 products per C
+// block, share 1.1: three parts 5 0.54, 13 0.73, two parts 0.82, 0.98).
+static bool lowp_groups(int prec, int m, double reuse, double share, bool full, int64_t nprod) {
     const char *e = getenv("BSM_LOWP_QUAD");
     if (e) return atoi(e) != 0;
     const bool many = nprod >= 400000;
-    if (prec == BSM_FP32) return many && (m == 32 || reuse >= (m <= 13 ? 14.0 : 32.0));
-    return many || static_cast<double>(nprod) * m >= 4e6;
+    if (prec == BSM_FP32)
+        return many && (m == 32 || reuse >= (m <= 13 ? 14.0 : 32.0)) &&
+               share >= (m == 32 ? 2.6 : m <= 13 ? 4.0 : 6.0);
+    if (!many && static_cast<double>(nprod) * m < 4e6) return false;
+    if (m <= 13 && reuse < 4.0 && full) return true;
+    return share >= (prec == BSM_SPLIT_BF16X3 ? (m == 32 ? 1.7 : 1.4) : (m == 32 ? 1.8 : 2.6));
 }
 
 // k segments of the group lists' symbolic walk (one workgroup per row group
@@ -236,19 +287,46 @@ int multiply(double alpha, Mat &A, Mat &B, double beta, Mat &C, double eps, int 
     int64_t *c_row_ptr = nullptr, *sums = nullptr;
     BSM_TRY(dalloc(&c_row_ptr, nbr + 1, s));      // becomes the new C's row_ptr
     const int64_t ns = nbr + 1;
-    int st = tmp.get(&sums, 3 * ns);
-    int64_t *c_nval = sums, *p_row_ptr = sums + ns;
+    int st = tmp.get(&sums, 3 * ns + 1);
+    int64_t *c_nval = sums, *p_row_ptr = sums + ns, *d_entries = sums + 3 * ns;
     double *flops_row = reinterpret_cast<double *>(sums + 2 * ns);
+    // the entries that 4 x 4 groups would have, where a rule below looks at them;
+    // counted along with the rest where as many products are to be expected
+    const int variant = smm_variant();
+    const bool mixed_sizes = !(A.uni_r && A.uni_c && B.uni_c);
+    const bool square = A.uni_r && A.uni_r == A.uni_c && A.uni_r == B.uni_c;
+    const bool may_group = variant == kSmmF64Quad && tau == 0.0 && !getenv("BSM_SMM_VARIANT") &&
+                           !getenv("BSM_QUAD_MIN_REUSE") &&
+                           (prec == BSM_FP64 ? mixed_sizes || (square && smm_tile_available(A.uni_r))
+                                             : square && smm_lowp_available(A.uni_r, A.uni_r, A.uni_r));
+    const double least_products =                               // below, no rule looks at them
+        mixed_sizes ? 1000.0 : prec == BSM_FP32 ? 4e5 :
+        prec == BSM_FP64 && smm_quad_available(A.uni_r, A.uni_r, A.uni_r) ? 1e6 : std::min(4e5, 4e6 / A.uni_r);
+    int32_t *b_groups = nullptr;
+    auto count = [&]() -> int {
+        BSM_TRY(tmp.get(&b_groups, std::max(1, B.nbrows)));
+        return count_entries(A, B, b_groups, d_entries, s);
+    };
+    if (st == BSM_OK && may_group &&
+        (sizes || static_cast<double>(A.nnzb) * static_cast<double>(B.nnzb) >= 0.5 * least_products * A.nbcols))
+        st = count();
     if (st == BSM_OK) st = sym_count(sa, c_row_ptr, c_nval, p_row_ptr, flops_row, s);
     if (st == BSM_OK) st = scan_i64(c_row_ptr, c_row_ptr, nbr, s);
     if (st == BSM_OK) st = scan_i64(c_nval, c_nval, nbr, s);
     if (st == BSM_OK) st = scan_i64(p_row_ptr, p_row_ptr, nbr, s);
-    std::vector<int64_t> h_crp(ns), h_sums(3 * ns);
+    std::vector<int64_t> h_crp(ns), h_sums(3 * ns + 1);
     if (st == BSM_OK) {
         hipError_t e = hipMemcpyAsync(h_crp.data(), c_row_ptr, sizeof(int64_t) * ns, hipMemcpyDeviceToHost, s);
-        if (e == hipSuccess) e = hipMemcpyAsync(h_sums.data(), sums, sizeof(int64_t) * 3 * ns, hipMemcpyDeviceToHost, s);
+        if (e == hipSuccess) e = hipMemcpyAsync(h_sums.data(), sums, sizeof(int64_t) * (3 * ns + 1), hipMemcpyDeviceToHost, s);
         if (e == hipSuccess) e = hipStreamSynchronize(s);
         if (e != hipSuccess) { set_error("multiply: reading sizes failed: %s", hipGetErrorString(e)); st = BSM_EDEVICE; }
+    }
+    if (st == BSM_OK && may_group && !b_groups && static_cast<double>(h_sums[2 * ns - 1]) >= least_products) {
+        st = count();
+        hipError_t e = hipSuccess;
+        if (st == BSM_OK) e = hipMemcpyAsync(&h_sums[3 * ns], d_entries, sizeof(int64_t), hipMemcpyDeviceToHost, s);
+        if (st == BSM_OK && e == hipSuccess) e = hipStreamSynchronize(s);
+        if (e != hipSuccess) { set_error("multiply: counting entries failed: %s", hipGetErrorString(e)); st = BSM_EDEVICE; }
     }
     if (st != BSM_OK) { dfree(c_row_ptr, s); return st; }
     const int64_t nnzb_c = h_crp[nbr];
@@ -288,14 +366,12 @@ int multiply(double alpha, Mat &A, Mat &B, double beta, Mat &C, double eps, int 
     // 5. tiled work order, then chunks of whole row bands with a bounded
     //    number of products
     const int rb = tile_rows();
-    const int variant = smm_variant();
     int64_t *worklist = nullptr, *worklist2 = nullptr;
     if (st == BSM_OK) st = keep_buf(&worklist, nnzb_c);
     if (st == BSM_OK) st = keep_buf(&worklist2, nnzb_c);  // target of the work-list sorts
     if (st == BSM_OK) st = tile_order(c_row_ptr, nc.col_idx, nbr, B.nbcols, rb, worklist, s);
     // mixed sizes in {5, 13, 23, 26}: groups over paired rows and columns
     // (FP64, no screening), unless another kernel variant is asked for
-    const bool mixed_sizes = !(A.uni_r && A.uni_c && B.uni_c);
     bool mixed_ok = true;
     for (const auto *v : {&A.h_rbs, &A.h_cbs, &B.h_cbs})
         for (int32_t b : *v)
@@ -326,41 +402,44 @@ int multiply(double alpha, Mat &A, Mat &B, double beta, Mat &C, double eps, int 
     // the quad kernel serves uniform sizes with a compile-time shape unless
     // the tuning table picks another kernel family for them
     const double reuse = nnzb_c ? static_cast<double>(nprod) / static_cast<double>(nnzb_c) : 0.0;
+    // products per entry of 4 x 4 groups (unknown: large), and a bound of the groups
+    const double share = b_groups && h_sums[3 * ns] > 0
+                             ? static_cast<double>(nprod) / static_cast<double>(h_sums[3 * ns]) : 1e300;
+    auto most_groups = [&]() {
+        const int64_t ncg = (B.nbcols + 3) / 4;
+        int64_t n = 0;
+        for (int32_t i = 0; i < nbr; i += 4) n += std::min(ncg, h_crp[std::min(nbr, i + 4)] - h_crp[i]);
+        return static_cast<double>(use_c || !b_groups ? n : std::min(n, h_sums[3 * ns]));
+    };
     bool use_quad = false;
     if (prec == BSM_FP64 && variant == kSmmF64Quad && A.uni_r && A.uni_c && B.uni_c &&
         smm_quad_available(A.uni_r, B.uni_c, A.uni_c)) {
         SmmParams tp;
         use_quad = !(table_lookup(A.uni_r, B.uni_c, A.uni_c, &tp) && tp.family != 3);
         if (use_quad && tau == 0.0 && !getenv("BSM_SMM_VARIANT"))
-            use_quad = fp64_groups(A.uni_r, reuse, nprod, sizes != nullptr);
+            use_quad = fp64_groups(A.uni_r, reuse, share, nprod, sizes != nullptr);
     }
     // the other uniform sizes: 4 x 4 groups instead of the run-time-shape
-    // kernel where the table has no choice for the size, C blocks have enough
-    // products, and the time saved exceeds the 0.1 ms that building the groups
-    // adds to a small multiply.  Products per C block, products, whole multiply
+    // kernel where the table has no choice for the size, C blocks and entries
+    // (`share`) have enough products, and the time saved exceeds the 0.1 ms that
+    // building the groups adds to a small multiply.  Products per C block, products, whole multiply
     // with the run-time-shape kernel and with groups: size 9 11.6, 1.9e5, 0.30
     // and 0.34 ms; 14.7, 2.1e6, 9.5 and 5.7; 172, 1.8e8, 90 and 29; size 17
     // 11.6, 1.9e5, 0.43 and 0.40; 172, 1.8e8, 196 and 83; size 31 11.6, 1.9e5,
     // 0.93 and 0.75; 172, 1.8e8, 617 and 251; size 4 11.6, 1.9e5, 0.25 and 0.30;
-    // 172, 1.8e8, 40 and 13.
+    // 172, 1.8e8, 40 and 13.  At share 1.1 the run-time-shape kernel and groups
+    // take 15.8 and 29.6 ms (size 4), 35 and 44 (9), 73 and 90 (17), 86 and 113 (22),
+    // 234 and 362 (31); 1.3 2.3 and 3.5 (4), 4.8 and 4.6 (9), 10.1 and 9.4 (17), 11.4
+    // and 12.7 (22); 1.55 5.4 and 6.3 (4), 27.5 and 25.2 (22), 74 and 76 (31); 1.9 11.1
+    // and 10.7 (4), 60 and 48 (22), 166 and 142 (31).
     if (prec == BSM_FP64 && variant == kSmmF64Quad && tau == 0.0 && A.uni_r && A.uni_r == A.uni_c &&
         A.uni_r == B.uni_c && !smm_quad_available(A.uni_r, A.uni_r, A.uni_r) && smm_tile_available(A.uni_r)) {
         SmmParams tp;
         use_quad = !table_lookup(A.uni_r, A.uni_r, A.uni_r, &tp) && reuse >= quad_min_reuse() &&
-                   static_cast<double>(nprod) * A.uni_r >= 5e5 * quad_min_reuse();
+                   static_cast<double>(nprod) * A.uni_r >= 5e5 * quad_min_reuse() &&
+                   share >= (A.uni_r < 9 ? 2.0 : A.uni_r <= 20 ? 1.25 : A.uni_r <= 24 ? 1.4 : 1.65);
     }
-    // mixed sizes: 4 x 4 groups of consecutive block rows and columns.  Whole
-    // multiplies with the one-block kernels and with groups:
-    //   any sizes ({4, 9, 13, 18, 22, 31}; the persistent kernel): 5e2 products
-    //     0.23 and 0.28 ms, 2e3 0.30 and 0.31, 2e4 0.55 and 0.46, 1.7e5 1.32 and
-    //     0.67; 14.7 products per C block 18.5 and 7.9 ms, 126 250 and 69;
-    //   {5, 13, 23, 26} (a launch per (m, n) class): all four sizes, 7e4 products
-    //     1.18 and 0.60 ms, 4e5 1.34 and 0.81, 1.1e6 1.74 and 1.66, 1.8e6 2.2 and
-    //     2.6; only 5 and 13 7e4 0.49 and 0.43, 3e5 0.54 and 0.53, 7e5 0.69 and 0.77;
-    //     1024 block rows, four sizes, 15 products per C block 6.8 and 8.2, 34 21.3
-    //     and 22.0, 47 31.0 and 30.1, 126 83 and 73; 5 and 13 47 10.6 and 12.6, 126
-    //     27.8 and 28.5; 13 and 23 47 30.3 and 29.9, 126 84 and 71.
-    // Classes that the table has a kernel for keep their launches.
+    // mixed sizes: classes that the table has a kernel for keep their launches
     bool use_mtile = false;
     if (prec == BSM_FP64 && tau == 0.0 && variant == kSmmF64Quad && mixed_sizes && nprod > 0) {
         auto distinct = [](const std::vector<int32_t> &v) {
@@ -368,8 +447,9 @@ int multiply(double alpha, Mat &A, Mat &B, double beta, Mat &C, double eps, int 
             for (int32_t b : v) m |= 1u << b;
             return __builtin_popcount(m);
         };
-        use_mtile = mixed_ok ? reuse >= 64.0 || nprod <= 50000 * distinct(A.h_rbs) * distinct(B.h_cbs)
-                             : nprod >= 4000;
+        use_mtile = mixed_groups(mixed_ok, reuse, share, static_cast<double>(nprod), static_cast<double>(nnzb_c),
+                                 most_groups(), 0.5 * flops / static_cast<double>(nprod),
+                                 mixed_ok ? distinct(A.h_rbs) * distinct(B.h_cbs) : 0);
         if (const char *e = getenv("BSM_MIXED_TILE")) use_mtile = atoi(e) != 0;
         for (int b = 0; mixed_ok && b < 16; ++b) {
             static const int sz[4] = {5, 13, 23, 26};
@@ -383,12 +463,13 @@ int multiply(double alpha, Mat &A, Mat &B, double beta, Mat &C, double eps, int 
     bool lowp_tile = false;
     if (prec != BSM_FP64 && variant == kSmmF64Quad && A.uni_r && A.uni_c && B.uni_c &&
         smm_lowp_available(A.uni_r, B.uni_c, A.uni_c))
-        use_quad = lowp_tile = lowp_groups(prec, A.uni_r, reuse, nprod);
+        use_quad = lowp_tile = lowp_groups(prec, A.uni_r, reuse, share,
+                                           static_cast<double>(nnzb_c) >= 8.0 * most_groups(), nprod);
     // group shape: quads, or other shapes on request (FP64 only); screening
     // runs through the quads' product masks
     int GR = 2, GC = 2;
     if (use_mtile || lowp_tile) GR = GC = 4;
-    else if (use_quad && prec == BSM_FP64 && tau == 0.0) quad_shape(A.uni_r, reuse, &GR, &GC);
+    else if (use_quad && prec == BSM_FP64 && tau == 0.0) quad_shape(A.uni_r, reuse, share, &GR, &GC);
     if (st == BSM_OK && tau > 0.0 && !use_quad) {
         set_error("product screening needs uniform block sizes 5, 6, 13, 23, 26 or 32 and the "
                   "default kernel variant");
@@ -757,6 +838,7 @@ int multiply(double alpha, Mat &A, Mat &B, double beta, Mat &C, double eps, int 
         sizes->nval_u = nval_c;
         sizes->nval = nc.nvalues;
         sizes->n_products = nprod;
+        sizes->share = share;
         sizes->n_groups = sum_groups;
         sizes->n_entries = sum_entries;
         sizes->gr = GR;

@@ -336,6 +336,71 @@ k_quad_stack(QuadSymArgs q) {
     if (FILL && q.tau2 > 0.0 && threadIdx.x == 0 && s_kept) atomicAdd(q.kept, s_kept);
 }
 
+// ---------------------------------------------------------------------------
+// Entries of the 4 x 4 groups without building them: entry (row group, k,
+// column group) exists where one of the four rows of A has a block in column k
+// and row k of B one in the column group.  So each k of the union of a row
+// group's rows adds the column groups of B's row k.  A few microseconds beside
+// the count of the products, which walks them one by one.
+__global__ void __launch_bounds__(kQuadThreads)
+k_row_col_groups(const int64_t *row_ptr, const int32_t *col_idx, int32_t nrows, int32_t *out,
+                 int64_t *entries) {
+    const int lane = threadIdx.x % kWave;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *entries = 0;
+    for (int32_t i = blockIdx.x * (kQuadThreads / kWave) + threadIdx.x / kWave; i < nrows;
+         i += gridDim.x * (kQuadThreads / kWave)) {
+        const int64_t b = row_ptr[i], e = row_ptr[i + 1];
+        int32_t n = 0;
+        for (int64_t t0 = b; t0 < e; t0 += kWave) {
+            const int64_t t = t0 + lane;
+            n += __popcll(__ballot(t < e && (t == b || col_idx[t - 1] / 4 != col_idx[t] / 4)));
+        }
+        if (lane == 0) out[i] = n;
+    }
+}
+
+__global__ void __launch_bounds__(kQuadThreads)
+k_count_entries(const int64_t *row_ptr, const int32_t *col_idx, int32_t nrows, const int32_t *col_groups,
+                int64_t *entries) {
+    __shared__ int64_t part[kQuadThreads / kWave];
+    const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
+    const int32_t ngroups = (nrows + 3) / 4;
+    int64_t n = 0;
+    for (int32_t g = blockIdx.x * (kQuadThreads / kWave) + w; g < ngroups; g += gridDim.x * (kQuadThreads / kWave)) {
+        for (int32_t i = 4 * g; i < 4 * g + 4 && i < nrows; ++i)
+            for (int64_t t = row_ptr[i] + lane; t < row_ptr[i + 1]; t += kWave) {
+                const int32_t k = col_idx[t];
+                bool seen = false;                     // in an earlier row of the group
+                for (int32_t r = 4 * g; r < i && !seen; ++r) {
+                    int64_t lo = row_ptr[r], hi = row_ptr[r + 1];
+                    const int64_t end = hi;
+                    while (lo < hi) {
+                        const int64_t mid = (lo + hi) >> 1;
+                        if (col_idx[mid] < k) lo = mid + 1; else hi = mid;
+                    }
+                    seen = lo < end && col_idx[lo] == k;
+                }
+                if (!seen) n += col_groups[k];
+            }
+    }
+    for (int o = kWave / 2; o > 0; o >>= 1) n += __shfl_xor(n, o, kWave);
+    if (lane == 0) part[w] = n;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int q = 1; q < kQuadThreads / kWave; ++q) n += part[q];
+        atomicAdd(reinterpret_cast<unsigned long long *>(entries), static_cast<unsigned long long>(n));
+    }
+}
+
+int count_entries(const Mat &A, const Mat &B, int32_t *per_row, int64_t *entries, hipStream_t s) {
+    auto grid = [](int64_t rows) { return std::min(grid_for(rows, kQuadThreads / kWave), 1024u); };
+    k_row_col_groups<<<grid(B.nbrows), kQuadThreads, 0, s>>>(B.row_ptr, B.col_idx, B.nbrows, per_row, entries);
+    k_count_entries<<<grid((A.nbrows + 3) / 4), kQuadThreads, 0, s>>>(A.row_ptr, A.col_idx, A.nbrows, per_row,
+                                                                     entries);
+    BSM_HIP(hipGetLastError());
+    return BSM_OK;
+}
+
 #define BSM_QUAD_SHAPES(X) X(2, 2) X(4, 4) X(4, 2)
 
 static int64_t quad_groups(const QuadSymArgs &q) {

@@ -135,10 +135,11 @@ int smm_bench(int m, int n, int k, int64_t n_c, int per_c, int n_prm, const SmmP
 
 // Quad kernel (smm_quad.hip): uniform m = n = k in {5, 6, 13, 23, 26, 32}.
 bool smm_quad_available(int m, int n, int k);
-// Group shape for uniform block size m and `reuse` products per C block: 4 x 4
-// or 2 x 2 (quads), as measured (smm_quad.hip), unless BSM_QUAD_GROUP asks for
-// 2 (2 x 2), 4 (4 x 4) or 42 (4 x 2, size 23) and m has quads.
-void quad_shape(int m, double reuse, int *gr, int *gc);
+// Group shape for uniform block size m, `reuse` products per C block and
+// `share` per entry of 4 x 4 groups: 4 x 4 or 2 x 2 (quads), as measured
+// (smm_quad.hip), unless BSM_QUAD_GROUP asks for 2 (2 x 2), 4 (4 x 4) or 42
+// (4 x 2, size 23) and m has quads.
+void quad_shape(int m, double reuse, double share, int *gr, int *gc);
 int launch_quad(const SmmArgs &a, hipStream_t s);
 bool smm_tile_available(int m);   // 4 x 4 groups of uniform size m (smm_tile.hip)
 int launch_tile(const SmmArgs &a, hipStream_t s);

@@ -410,11 +410,16 @@ bool smm_quad_available(int m, int n, int k) {
 //   26  34: 47.2 and 48.1, 92: 128.0 and 125.2, 172: 233 and 219;
 //   32  172: 440 and 443 (one group per CU, and rows of 32 doubles fall on
 //       the same LDS banks).
-// The other sizes have no quads.
-void quad_shape(int m, double reuse, int *gr, int *gc) {
+// With fewer than about two products per 4 x 4 entry (`share`; sizes 13 and
+// 23), five (5, 6, 26), quads are faster: 23 share 1.1 77 and 113 ms, 1.4 103 and
+// 125, 1.9 48 and 48, 2.2 546 and 500; 13 1.4 42 and 52, 2.0 19.2 and 19.3, 2.2 204
+// and 202; 5 2.2 93 and 106, 4.6 34 and 28; 26 2.2 958 and 1259, 4.6 403 and 395,
+// 7.7 717 and 685.  The other sizes have no quads.
+void quad_shape(int m, double reuse, double share, int *gr, int *gc) {
     const char *e = getenv("BSM_QUAD_GROUP");
-    const bool tile = !smm_quad_available(m, m, m) || m == 23 || (m == 13 && reuse >= 24.0) ||
-                      (m != 13 && m != 32 && reuse >= 64.0);
+    const bool tile = !smm_quad_available(m, m, m) || (m == 23 && share >= 1.9) ||
+                      (m == 13 && reuse >= 24.0 && share >= 2.1) ||
+                      (m != 13 && m != 23 && m != 32 && reuse >= 64.0 && share >= 4.5);
     const int g = e && smm_quad_available(m, m, m) ? atoi(e) : (tile ? 4 : 2);
     *gr = *gc = 2;
     if (g == 4) { *gr = 4; *gc = 4; }
