@@ -120,7 +120,8 @@ struct MulSizes {
 // plan (may be NULL): on success receives the retained symbolic state.
 // tau > 0: product-level norm screening (terms with ||A_ik||^2 ||B_kj||^2 <
 // tau^2 left out; FP64 group kernel only).  sizes (may be NULL): receives
-// the sizes above.
+// the sizes above, for graphs that take over (FP64 then runs in groups from 8
+// products per C block on).
 int multiply(double alpha, Mat &A, Mat &B, double beta, Mat &C, double eps,
              int norm, int prec, bsm_mult_stats *stats, hipStream_t s,
              MulPlan **plan = nullptr, double tau = 0.0, MulSizes *sizes = nullptr);

@@ -68,9 +68,10 @@ static double quad_min_reuse() {
 // 4.6, 25 6.3 and 6.9, 92 22 and 30; 23 9 3.3 and 2.8, 11 9.0 and 8.6, 15 14.9
 // and 15.4, 18 21.7 and 24.0; 26 18 43.5 and 39.4, 47 66.4 and 65.0, 92 126 and
 // 133; 32 18 74.0 and 73.4, 25 56.4 and 56.8, 92 242 and 250.  Few products
-// (7e5, reuse 18): 13 0.59 and 0.43, 23 0.96 and 0.74.  The sign iteration (`iter`)
-// has its multiplies from graphs where they run in groups, and keeps to them.
-// Those are neighbour lists along a Morton curve, about 5 products per 4 x 4
+// (7e5, reuse 18): 13 0.59 and 0.43, 23 0.96 and 0.74.  A sign iteration with
+// device-sized graphs (`iter`) has its multiplies from the graphs where they run
+// in groups, and keeps to them.
+// All of those are neighbour lists along a Morton curve, about 5 products per 4 x 4
 // entry and more (`share`).  Where neighbouring rows and columns have little in
 // common, a group stages an operand for one or two products; one block and
 // groups then, ms: 23 share 1.1 69 and 113, 1.4 100 and 125, 1.9 48 and 48, 2.2

@@ -522,7 +522,7 @@ int sign_iterate(Mat &H, double mu, const bsm_sign_opts &o, Mat **x_out, bsm_sig
         if (!update_only) {
             if (!have_y) {
                 rc = multiply(1.0, *X, *X, 0.0, *Y, o.eps_filter, o.norm, prec, &ms, s,
-                              want_graph ? &R.psq : nullptr, o.eps_screen, &sz_sq);
+                              want_graph ? &R.psq : nullptr, o.eps_screen, G ? &sz_sq : nullptr);
                 st->n_multiplies++;
                 st->flops += ms.flops;
                 st->n_products += ms.n_products;
@@ -561,7 +561,7 @@ int sign_iterate(Mat &H, double mu, const bsm_sign_opts &o, Mat **x_out, bsm_sig
         }
         const int64_t x_before = X->nnzb;
         rc = multiply(-0.5, *X, *Y, 1.5, *X, o.eps_filter, o.norm, prec, &ms, s,
-                      (want_graph && R.psq) ? &R.pup : nullptr, o.eps_screen, &sz_up);
+                      (want_graph && R.psq) ? &R.pup : nullptr, o.eps_screen, G ? &sz_up : nullptr);
         st->n_multiplies++;
         st->flops += ms.flops;
         st->n_products += ms.n_products;

@@ -262,3 +262,33 @@ def test_use_graph_value_checked():
     with pytest.raises(bsm.BsmError) as e:
         _run(h, 0.0, 1e-8, 3)
     assert e.value.status == bsm.EINVAL
+
+
+def _dense_enough(n, b, fill, seed):
+    """Symmetric H with a gap at 0 and about `fill` of its blocks stored."""
+    rng = np.random.default_rng(seed)
+    mask = rng.random((n, n)) < fill
+    mask = np.triu(mask, 1)
+    mask = mask | mask.T | np.eye(n, dtype=bool)
+    d = rng.standard_normal((n * b, n * b)) / (4.0 * np.sqrt(n * b))
+    d = np.where(np.repeat(np.repeat(mask, b, 0), b, 1), 0.5 * (d + d.T), 0.0)
+    d[np.arange(n * b), np.arange(n * b)] += np.where(rng.random(n * b) < 0.3, -1.5, 1.5)
+    r, c = np.nonzero(mask)
+    sizes = np.full(n, b, dtype=np.int32)
+    vals = d.reshape(n, b, n, b).transpose(0, 2, 1, 3)[r, c]
+    ptr = np.concatenate([[0], np.cumsum(mask.sum(1))]).astype(np.int64)
+    return synth.BSR(sizes, sizes, ptr, c.astype(np.int32), vals.reshape(-1))
+
+
+@pytest.mark.parametrize("order,mode", [(2, 0), (2, 2), (3, 0)])
+def test_groups_are_for_device_sized_graphs(order, mode):
+    """About 10 products per C block: a multiply takes one C block per wave,
+    also in iterations that no device-sized graphs take over."""
+    from paper_2003_03868_amd import bsm
+    h = _dense_enough(24, 13, 0.62, 1)
+    d = to_dev(h)
+    o = bsm.bsm_sign_opts_default()
+    o.eps_filter, o.tol, o.order, o.use_graph, o.fixed_iters = 0.0, 0.0, order, mode, 1
+    st, xh, _ = bsm.bsm_sign_iterate(d.handle, 0.0, o)
+    bsm.Matrix(xh, h.row_blk_size, h.col_blk_size)
+    assert st == bsm.OK and "k_smm_f64_fixed" in bsm.bsm_last_smm_kernel()
