@@ -112,7 +112,7 @@ struct MulSizes {
     double share = 1e300;    // products per entry of 4 x 4 groups (large: not counted)
     int64_t n_groups = 0;    // groups of C blocks of the group kernel, over all chunks
     int64_t n_entries = 0;   // their entries
-    int gr = 0;              // rows of a group (0: as in the graphs that counted them)
+    int gr = 0;              // rows of a group
     bool groups = false;     // an FP64 group kernel did the products (uniform sizes, or
                              // mixed sizes in one launch)
 };

@@ -326,6 +326,7 @@ GraphIter *gi_create(hipStream_t s, double eps, int norm) {
 
 void gi_destroy(GraphIter *g) { delete g; }
 bool gi_on(const GraphIter *g) { return g && g->on; }
+int gi_group_rows(const GraphIter *g) { return g->gr; }
 int64_t gi_x_nnzb(const GraphIter *g) { return g->x_nnzb; }
 
 int GraphIter::alloc(const Caps &c) {
@@ -577,10 +578,6 @@ int gi_enter(GraphIter *g, Mat &X, Mat &Y, const MulSizes &sq, const MulSizes &u
             g->gr = g->gc = 2;
             mixed_pairs(X.h_rbs, X.h_cbs, &g->mp);
             g->nrg = g->mp.band_g0.back();
-        } else {
-            quad_shape(g->b, sq.nnzb_u ? static_cast<double>(sq.n_products) / static_cast<double>(sq.nnzb_u) : 0.0,
-                       sq.share, &g->gr, &g->gc);
-            g->nrg = (static_cast<int64_t>(g->nbr) + g->gr - 1) / g->gr;
         }
         g->nseg = quad_ksegments(X.nbcols);
         g->kseg = (X.nbcols + g->nseg - 1) / g->nseg;
@@ -588,6 +585,14 @@ int gi_enter(GraphIter *g, Mat &X, Mat &Y, const MulSizes &sq, const MulSizes &u
         for (hipEvent_t &e : g->ev)
             if (!e) BSM_HIP(hipEventCreate(&e));
     }
+    // the group shape for the products as they are now (X fills up, and the
+    // graphs are entered again after an overflow); another shape, other graphs
+    int gr = 2, gc = 2;
+    if (!g->mixed)
+        quad_shape(g->b, sq.nnzb_u ? static_cast<double>(sq.n_products) / static_cast<double>(sq.nnzb_u) : 0.0,
+                   std::min(sq.share, up.share), &gr, &gc);
+    const int64_t nrg = g->mixed ? g->nrg : (static_cast<int64_t>(g->nbr) + gr - 1) / gr;
+    const bool reshaped = nrg != g->nrg || gr != g->gr || gc != g->gc;
     // capacities: the sizes times the headroom, plus a little slack (none
     // at headroom 1, so that any growth overflows), within the structural
     // bounds, at least 1
@@ -601,27 +606,31 @@ int gi_enter(GraphIter *g, Mat &X, Mat &Y, const MulSizes &sq, const MulSizes &u
     const int64_t dense = static_cast<int64_t>(g->nbr) * g->nbc;
     const int64_t dense_v = X.nrows * X.ncols;
     const int64_t ncg = g->mixed ? static_cast<int64_t>(g->mp.cmap.size() / 2)
-                                 : (g->nbc + g->gc - 1) / g->gc;
+                                 : (g->nbc + gc - 1) / gc;
     Caps want;
     want.c = grow(std::max(sq.nnzb_u, up.nnzb_u), dense, m[0]);
     want.cv = grow(std::max(sq.nval_u, up.nval_u), dense_v, m[0]);
     // a 4 x 4 group (entry) is up to four 2 x 2 ones
-    auto own = [&](const MulSizes &z, int64_t v) { return z.gr > g->gr ? 4 * v : v; };
-    want.g = grow(std::max(own(sq, sq.n_groups), own(up, up.n_groups)), g->nrg * ncg, m[1]);
+    auto own = [&](const MulSizes &z, int64_t v) { return z.gr > gr ? 4 * v : v; };
+    want.g = grow(std::max(own(sq, sq.n_groups), own(up, up.n_groups)), nrg * ncg, m[1]);
     want.e = grow(std::max(own(sq, sq.n_entries), own(up, up.n_entries)), INT32_MAX, m[2]);
     want.x = std::max(X.nnzb, grow(std::max(up.nnzb, X.nnzb), dense, m[3]));
     want.xv = std::max(X.nvalues, grow(std::max(up.nval, X.nvalues), dense_v, m[3]));
     want.y = grow(sq.nnzb, dense, m[4]);
     want.yv = grow(sq.nval, dense_v, m[4]);
     if (want.c > INT32_MAX || std::max({sq.n_entries, up.n_entries}) > INT32_MAX) return BSM_OK;
-    const Caps &c = g->cap;
-    if (want.c > c.c || want.cv > c.cv || want.g > c.g || want.e > c.e || want.x > c.x ||
+    Caps c = g->cap;
+    if (reshaped) c.g = c.e = 0;
+    if (reshaped || want.c > c.c || want.cv > c.cv || want.g > c.g || want.e > c.e || want.x > c.x ||
         want.xv > c.xv || want.y > c.y || want.yv > c.yv) {
         Caps n;
         n.c = std::max(want.c, c.c); n.cv = std::max(want.cv, c.cv);
         n.g = std::max(want.g, c.g); n.e = std::max(want.e, c.e);
         n.x = std::max(want.x, c.x); n.xv = std::max(want.xv, c.xv);
         n.y = std::max(want.y, c.y); n.yv = std::max(want.yv, c.yv);
+        g->gr = gr;
+        g->gc = gc;
+        g->nrg = nrg;
         const int r = g->alloc(n);
         if (r == BSM_ENOMEM) {
             // device memory too small for the fixed-capacity buffers: the

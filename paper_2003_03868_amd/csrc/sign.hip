@@ -396,6 +396,8 @@ int sign_iterate(Mat &H, double mu, const bsm_sign_opts &o, Mat **x_out, bsm_sig
                 sz_sq.nnzb = gs.nnzb;
                 sz_sq.nval_u = gs.nval_u;
                 sz_sq.nval = gs.nval;
+                sz_sq.n_products = gs.n_products;
+                sz_sq.gr = gi_group_rows(G);
                 sz_sq.n_groups = gs.n_groups;
                 sz_sq.n_entries = gs.n_entries;
                 sz_sq.groups = true;

@@ -292,3 +292,16 @@ def test_groups_are_for_device_sized_graphs(order, mode):
     st, xh, _ = bsm.bsm_sign_iterate(d.handle, 0.0, o)
     bsm.Matrix(xh, h.row_blk_size, h.col_blk_size)
     assert st == bsm.OK and "k_smm_f64_fixed" in bsm.bsm_last_smm_kernel()
+
+
+def test_group_shape_follows_the_products(monkeypatch):
+    """Size 13: about 20 products per C block when the graphs are entered
+    (2 x 2 groups), 40 when they are entered again after an overflow (4 x 4)."""
+    from paper_2003_03868_amd import bsm
+    monkeypatch.setenv("BSM_GRAPH_HEADROOM", "1")
+    h = _dense_enough(40, 13, 0.7, 2)
+    ref = _run(h, 0.0, 1e-10, 0)
+    got = _run(h, 0.0, 1e-10, 1)
+    _same_run(ref, got)
+    assert got[2].graph_fallbacks == 1 and got[2].graph_replays > 1
+    assert "k_smm_f64_tile<13" in bsm.bsm_last_smm_kernel()   # the last one captured
