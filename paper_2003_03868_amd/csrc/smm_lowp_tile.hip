@@ -344,6 +344,15 @@ void pack_side(const double *v, int64_t n, bool b_side, uint32_t *out, hipStream
 // 7.0 / 6.9, FP32 6.5 / 6.1 / 6.7.
 constexpr int lowp_eps(int s) { return s <= 5 ? 4 : s <= 13 ? 2 : 1; }
 
+template <int S, int T>
+static int launch_size(const SmmArgs &a, hipStream_t s) {
+    constexpr int EPS = lowp_eps(S);
+    note_kernelf("k_lowp_tile<%d, %d, %d>", S, T, EPS);
+    return launch_groups(a, 512, [&](const SmmArgs &b, unsigned grid) {
+        k_lowp_tile<S, T, EPS><<<grid, 512, 0, s>>>(b);
+    });
+}
+
 #define BSM_LT_SIZES(X) X(5) X(13) X(23) X(26) X(32)
 
 int64_t lowp_image_words(int64_t nblocks, int size, int prec) {
@@ -377,11 +386,9 @@ int launch_lowp_tile(const SmmArgs &a, hipStream_t s) {
     switch (a.uni_m) {
 #define BSM_LT(S)                                                                                      \
         case S:                                                                                        \
-            return launch_groups(a, 512, [&](const SmmArgs &b, unsigned grid) {                        \
-                if (b.prec == BSM_FP32) BSM_LAUNCH((k_lowp_tile<S, 0, lowp_eps(S)>), grid, 512, 0, s)(b); \
-                else if (b.prec == BSM_SPLIT_BF16) BSM_LAUNCH((k_lowp_tile<S, 2, lowp_eps(S)>), grid, 512, 0, s)(b); \
-                else BSM_LAUNCH((k_lowp_tile<S, 3, lowp_eps(S)>), grid, 512, 0, s)(b);                 \
-            });
+            return a.prec == BSM_FP32         ? launch_size<S, 0>(a, s)                                \
+                   : a.prec == BSM_SPLIT_BF16 ? launch_size<S, 2>(a, s)                                \
+                                              : launch_size<S, 3>(a, s);
         BSM_LT_SIZES(BSM_LT)
 #undef BSM_LT
         default: set_error("no reduced-precision tile kernel for block size %d", a.uni_m); return BSM_EINVAL;

@@ -233,15 +233,21 @@ k_smm_f64_tile(SmmArgs a) {
 // 30.7 / 27.5 / 26.1, 13 38.1 / 36.1, 17 80.9 / 79.6.
 constexpr int tile_eps(int s) { return s <= 12 ? 4 : s <= 17 ? 2 : 1; }
 
+template <int S>
+static int launch_size(const SmmArgs &a, hipStream_t s) {
+    constexpr int EPS = tile_eps(S), WPE = S <= 24 ? 8 : 4;
+    note_kernelf("k_smm_f64_tile<%d, %d, %d>", S, EPS, WPE);
+    return launch_groups(a, 1024, [&](const SmmArgs &b, unsigned grid) {
+        k_smm_f64_tile<S, EPS, WPE><<<grid, 1024, 0, s>>>(b);
+    });
+}
+
 bool smm_tile_available(int m) { return m >= 4 && m <= kMaxBlock; }
 
 int launch_tile(const SmmArgs &a, hipStream_t s) {
     switch (a.uni_m) {
 #define BSM_TILE(S) \
-        case S:                                                                                \
-            return launch_groups(a, 1024, [&](const SmmArgs &b, unsigned grid) {               \
-                BSM_LAUNCH((k_smm_f64_tile<S, tile_eps(S), (S <= 24 ? 8 : 4)>), grid, 1024, 0, s)(b); \
-            });
+        case S: return launch_size<S>(a, s);
         BSM_TILE(4) BSM_TILE(5) BSM_TILE(6) BSM_TILE(7) BSM_TILE(8) BSM_TILE(9) BSM_TILE(10)
         BSM_TILE(11) BSM_TILE(12) BSM_TILE(13) BSM_TILE(14) BSM_TILE(15) BSM_TILE(16) BSM_TILE(17)
         BSM_TILE(18) BSM_TILE(19) BSM_TILE(20) BSM_TILE(21) BSM_TILE(22) BSM_TILE(23) BSM_TILE(24)
