@@ -23,7 +23,7 @@ __device__ inline void group_barrier() {
 // address `slot`: 64 a copy, the lanes' bytes consecutive at m0.
 // voff = 16 lane; every lane of the wave is active, the last copy runs with
 // the lanes it needs.  The five wait states cover a source address that a
-// lane read has just written.
+// lane read has just written; M0 is declared as written, EXEC is as before.
 template <int PIECES>
 __device__ inline void stage_pieces(uint64_t src, uint32_t slot, uint32_t voff) {
     constexpr int FULL = PIECES / 64, REST = PIECES % 64;
@@ -34,18 +34,18 @@ __device__ inline void stage_pieces(uint64_t src, uint32_t slot, uint32_t voff) 
                      "global_load_lds_dwordx4 %1, %2 offset:1024\n\t"
                      "global_load_lds_dwordx4 %1, %2 offset:2048\n\t"
                      "global_load_lds_dwordx4 %1, %2 offset:3072"
-                     :: "s"(slot + 4096 * q), "v"(voff + 4096 * q), "s"(src) : "memory");
+                     :: "s"(slot + 4096 * q), "v"(voff + 4096 * q), "s"(src) : "m0", "memory");
 #pragma unroll
     for (int q = FULL / 4 * 4; q < FULL; ++q)
         asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\t"
                      "global_load_lds_dwordx4 %1, %2"
-                     :: "s"(slot + 1024 * q), "v"(voff + 1024 * q), "s"(src) : "memory");
+                     :: "s"(slot + 1024 * q), "v"(voff + 1024 * q), "s"(src) : "m0", "memory");
     if constexpr (REST > 0)
         asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\ts_mov_b64 exec, %3\n\t"
                      "global_load_lds_dwordx4 %1, %2\n\t"
                      "s_mov_b64 exec, -1"
                      :: "s"(slot + 1024 * FULL), "v"(voff + 1024 * FULL), "s"(src),
-                        "s"((1ull << REST) - 1) : "memory");
+                        "s"((1ull << REST) - 1) : "m0", "memory");
 }
 
 }  // namespace bsm

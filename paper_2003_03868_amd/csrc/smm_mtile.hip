@@ -55,7 +55,7 @@ __device__ inline void stage_pieces(uint64_t src, uint32_t dst, int pieces, uint
         asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\ts_mov_b64 exec, %3\n\t"
                      "global_load_lds_dwordx4 %1, %2\n\t"
                      "s_mov_b64 exec, -1"
-                     :: "s"(dst + p * 16), "v"(voff + p * 16), "s"(src), "s"(ex) : "memory");
+                     :: "s"(dst + p * 16), "v"(voff + p * 16), "s"(src), "s"(ex) : "m0", "memory");
     }
 }
 

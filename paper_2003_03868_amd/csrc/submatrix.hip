@@ -53,7 +53,7 @@ typedef __attribute__((address_space(3))) double lds_double;
 // the registers.
 __device__ inline void dma16(uint32_t slot, uint32_t voff, const double *src) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %1, %2"
-                 :: "s"(slot), "v"(voff), "s"(reinterpret_cast<uint64_t>(src)) : "memory");
+                 :: "s"(slot), "v"(voff), "s"(reinterpret_cast<uint64_t>(src)) : "m0", "memory");
 }
 
 // One 64 x 64 tile of D = A B (mode 0: A = B = X, D = Y; mode 1: A = X,
