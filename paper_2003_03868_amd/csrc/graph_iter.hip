@@ -466,7 +466,6 @@ int GraphIter::mult_smm(const Mat &A, const Mat &B, const Mat *Cin, double alpha
     a.alpha = alpha; a.beta = beta;
     a.sq_out = sq; a.mx_out = mx; a.flags = &rec->flags;
     a.max_m = A.max_rbs; a.max_n = B.max_cbs; a.max_k = A.max_cbs;
-    a.nbr = nbr; a.nbc = nbc;
     a.uni_m = A.uni_r; a.uni_n = B.uni_c; a.uni_k = A.uni_c;
     a.fused_ok = mixed ? 1 : 0;
     a.prec = BSM_FP64;

@@ -48,4 +48,22 @@ __device__ inline void stage_pieces(uint64_t src, uint32_t slot, uint32_t voff) 
                         "s"((1ull << REST) - 1) : "m0", "memory");
 }
 
+// The same with a number of pieces known at run time.
+__device__ inline void stage_pieces(uint64_t src, uint32_t slot, int pieces, uint32_t voff) {
+    for (int p = 0; p < pieces; p += 64) {
+        const uint64_t ex = pieces - p >= 64 ? ~0ull : (1ull << (pieces - p)) - 1ull;
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\ts_mov_b64 exec, %3\n\t"
+                     "global_load_lds_dwordx4 %1, %2\n\t"
+                     "s_mov_b64 exec, -1"
+                     :: "s"(slot + p * 16), "v"(voff + p * 16), "s"(src), "s"(ex) : "m0", "memory");
+    }
+}
+
+// 16 bytes a lane from src + voff to consecutive LDS bytes at `slot`, past
+// the registers.
+__device__ inline void dma16(uint32_t slot, uint32_t voff, const double *src) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %1, %2"
+                 :: "s"(slot), "v"(voff), "s"(reinterpret_cast<uint64_t>(src)) : "m0", "memory");
+}
+
 }  // namespace bsm

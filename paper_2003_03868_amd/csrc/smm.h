@@ -78,7 +78,7 @@ struct SmmArgs {
     const int64_t *q_order;     // group of work item i (NULL: identity)
     int32_t q_gr, q_gc;         // group shape
     int64_t q_first, q_count;   // groups of this launch (smm_group.h)
-    int32_t nbr, nbc;           // block rows and columns of C
+    int32_t nbr, nbc;           // block rows and columns of C (mixed-size groups)
     const int32_t *q_pm;        // product mask per entry (bit GC r + c), NULL: all products
 };
 

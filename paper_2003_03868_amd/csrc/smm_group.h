@@ -1,5 +1,5 @@
 // What the kernels over 4 x 4 groups of C blocks share: the work item of a
-// workgroup, and launches of any number of groups.
+// workgroup, reductions over a wave, and launches of any number of groups.
 #pragma once
 
 #include <algorithm>
@@ -18,6 +18,15 @@ __device__ inline int64_t group_item(const SmmArgs &a) {
     if (static_cast<int64_t>(blockIdx.x / kXcds) >= per) return -1;
     const int64_t it = static_cast<int64_t>(blockIdx.x % kXcds) * per + blockIdx.x / kXcds;
     return it < n ? a.q_first + it : -1;
+}
+
+__device__ inline double group_wave_sum(double v) {
+    for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
+    return v;
+}
+__device__ inline double group_wave_max(double v) {
+    for (int o = kWave / 2; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, kWave));
+    return v;
 }
 
 // launch(args, grid) over all groups, one workgroup of `threads` each, in

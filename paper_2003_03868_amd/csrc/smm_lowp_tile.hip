@@ -84,15 +84,6 @@ __global__ __launch_bounds__(64) void k_pack_image(const double *v, int64_t n, u
         pack_image<S, T, B>(v + t * (S * S), reinterpret_cast<char *>(out) + t * LImage<S, T>::BYTES);
 }
 
-__device__ inline double l_wave_sum(double v) {
-    for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-    return v;
-}
-__device__ inline double l_wave_max(double v) {
-    for (int o = kWave / 2; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, kWave));
-    return v;
-}
-
 // Wave w owns C blocks w and w + 8 of the group in the order of the FP64 tile
 // kernel (a SIMD's blocks are of different rows and columns) and stages operand
 // w (A rows 0 .. 3, B columns 0 .. 3) of every entry.  Two stages of EPS entries
@@ -313,8 +304,8 @@ k_lowp_tile(SmmArgs a) {
                 mx = fmax(mx, fabs(v));
             }
         }
-        sq = l_wave_sum(sq);
-        mx = l_wave_max(mx);
+        sq = group_wave_sum(sq);
+        mx = group_wave_max(mx);
         if (lane == 0) {
             a.sq_out[cb] = sq;
             a.mx_out[cb] = mx;

@@ -32,31 +32,10 @@ namespace {
 
 typedef __attribute__((address_space(3))) double lds_double;
 
-__device__ inline double t_wave_sum(double v) {
-    for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-    return v;
-}
-__device__ inline double t_wave_max(double v) {
-    for (int o = kWave / 2; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, kWave));
-    return v;
-}
-
 __device__ inline int64_t lane64(int64_t v, int l) {
     const uint32_t lo = __builtin_amdgcn_readlane(static_cast<int>(v), l);
     const uint32_t hi = __builtin_amdgcn_readlane(static_cast<int>(v >> 32), l);
     return static_cast<int64_t>((static_cast<uint64_t>(hi) << 32) | lo);
-}
-
-// `pieces` 16-byte pieces from src to LDS, 64 a copy, the last with the lanes it
-// needs (every lane of the wave is active; voff = 16 lane).
-__device__ inline void stage_pieces(uint64_t src, uint32_t dst, int pieces, uint32_t voff) {
-    for (int p = 0; p < pieces; p += kWave) {
-        const uint64_t ex = pieces - p >= kWave ? ~0ull : (1ull << (pieces - p)) - 1ull;
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\ts_mov_b64 exec, %3\n\t"
-                     "global_load_lds_dwordx4 %1, %2\n\t"
-                     "s_mov_b64 exec, -1"
-                     :: "s"(dst + p * 16), "v"(voff + p * 16), "s"(src), "s"(ex) : "m0", "memory");
-    }
 }
 
 // What a wave's products of one C block share.
@@ -170,8 +149,8 @@ __device__ inline void store(const SmmArgs &a, int64_t c, int m, int n, int lane
                 mx = fmax(mx, fabs(v));
             }
         }
-    sq = t_wave_sum(sq);
-    mx = t_wave_max(mx);
+    sq = group_wave_sum(sq);
+    mx = group_wave_max(mx);
     if (lane == 0) {
         a.sq_out[c] = sq;
         a.mx_out[c] = mx;

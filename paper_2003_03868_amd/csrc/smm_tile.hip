@@ -50,15 +50,6 @@ struct TShape {
     static constexpr int TAIL = (8 * H * S - B2 + 64) * 8;
 };
 
-__device__ inline double t_wave_sum(double v) {
-    for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-    return v;
-}
-__device__ inline double t_wave_max(double v) {
-    for (int o = kWave / 2; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, kWave));
-    return v;
-}
-
 // The wave's product of an entry: 4 x 4 x 4 steps in ascending k.  A rows and
 // B columns past S read what follows in LDS, which reaches only accumulator
 // elements that are never stored; the k's past S are zeroed on both sides.
@@ -216,8 +207,8 @@ k_smm_f64_tile(SmmArgs a) {
                 mx = fmax(mx, fabs(v));
             }
         }
-    sq = t_wave_sum(sq);
-    mx = t_wave_max(mx);
+    sq = group_wave_sum(sq);
+    mx = group_wave_max(mx);
     if (lane == 0) {
         a.sq_out[c] = sq;
         a.mx_out[c] = mx;

@@ -49,13 +49,6 @@ struct SubGemm {
 
 typedef __attribute__((address_space(3))) double lds_double;
 
-// 16 bytes a lane from src + voff to consecutive LDS bytes at `slot`, past
-// the registers.
-__device__ inline void dma16(uint32_t slot, uint32_t voff, const double *src) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %1, %2"
-                 :: "s"(slot), "v"(voff), "s"(reinterpret_cast<uint64_t>(src)) : "m0", "memory");
-}
-
 // One 64 x 64 tile of D = A B (mode 0: A = B = X, D = Y; mode 1: A = X,
 // B = Y, D = 1.5 X - 0.5 A B into the other X buffer).  Four waves, each a
 // 32 x 32 quarter as 2 x 2 tiles of V_MFMA_F64_16X16X4_F64: lane l feeds
