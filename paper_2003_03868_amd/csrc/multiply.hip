@@ -58,6 +58,9 @@ static double quad_min_reuse() {
     return e ? atof(e) : 8.0;
 }
 
+// The same for a size m with a one-block kernel of its own (below).
+static double fp64_least_reuse(int m) { return m == 23 ? 12.5 : (m == 13 || m == 32) ? 20.0 : 64.0; }
+
 // FP64 groups for a size m with a one-block kernel of its own, `reuse`
 // products per C block, unless BSM_SMM_VARIANT names a kernel or screening
 // needs the groups.  Their lists cost a symbolic pass and two host waits
@@ -80,8 +83,7 @@ static double quad_min_reuse() {
 // 790 and 685; 32 1.9 120 and 129, 4.6 658 and 668, 7.7 1402 and 1339.
 static bool fp64_groups(int m, double reuse, double share, int64_t nprod, bool iter) {
     if (iter || getenv("BSM_QUAD_MIN_REUSE")) return reuse >= quad_min_reuse();
-    const double least = m == 23 ? 12.5 : (m == 13 || m == 32) ? 20.0 : 64.0;
-    return reuse >= least && nprod >= 1000000 && share >= (m == 23 || m == 13 ? 2.1 : 5.0);
+    return reuse >= fp64_least_reuse(m) && nprod >= 1000000 && share >= (m == 23 || m == 13 ? 2.1 : 5.0);
 }
 
 // Mixed sizes: 4 x 4 groups of consecutive block rows and columns.  Whole
@@ -288,11 +290,17 @@ int multiply(double alpha, Mat &A, Mat &B, double beta, Mat &C, double eps, int 
     int64_t *c_row_ptr = nullptr, *sums = nullptr;
     BSM_TRY(dalloc(&c_row_ptr, nbr + 1, s));      // becomes the new C's row_ptr
     const int64_t ns = nbr + 1;
-    int st = tmp.get(&sums, 3 * ns + 1);
+    const int parts = count_entries_parts(A);
+    int st = tmp.get(&sums, 3 * ns + parts);
     int64_t *c_nval = sums, *p_row_ptr = sums + ns, *d_entries = sums + 3 * ns;
     double *flops_row = reinterpret_cast<double *>(sums + 2 * ns);
-    // the entries that 4 x 4 groups would have, where a rule below looks at them;
-    // counted along with the rest where as many products are to be expected
+    if (st == BSM_OK) st = sym_count(sa, c_row_ptr, c_nval, p_row_ptr, flops_row, s);
+    if (st == BSM_OK) st = scan_i64(c_row_ptr, c_row_ptr, nbr, s);
+    if (st == BSM_OK) st = scan_i64(c_nval, c_nval, nbr, s);
+    if (st == BSM_OK) st = scan_i64(p_row_ptr, p_row_ptr, nbr, s);
+    // the entries that 4 x 4 groups would have, where a rule below looks at them:
+    // counted along with the rest (8 us) where as many products are to be
+    // expected, by themselves for the sizes that seldom have enough per C block
     const int variant = smm_variant();
     const bool mixed_sizes = !(A.uni_r && A.uni_c && B.uni_c);
     const bool square = A.uni_r && A.uni_r == A.uni_c && A.uni_r == B.uni_c;
@@ -300,32 +308,31 @@ int multiply(double alpha, Mat &A, Mat &B, double beta, Mat &C, double eps, int 
                            !getenv("BSM_QUAD_MIN_REUSE") &&
                            (prec == BSM_FP64 ? mixed_sizes || (square && smm_tile_available(A.uni_r))
                                              : square && smm_lowp_available(A.uni_r, A.uni_r, A.uni_r));
+    const bool own = prec == BSM_FP64 && square && smm_quad_available(A.uni_r, A.uni_r, A.uni_r);
     const double least_products =                               // below, no rule looks at them
-        mixed_sizes ? 1000.0 : prec == BSM_FP32 ? 4e5 :
-        prec == BSM_FP64 && smm_quad_available(A.uni_r, A.uni_r, A.uni_r) ? 1e6 : std::min(4e5, 4e6 / A.uni_r);
+        mixed_sizes ? 1000.0 : own ? 1e6 : prec == BSM_FP32 ? 4e5 : std::min(4e5, 4e6 / std::max(1, A.uni_r));
     int32_t *b_groups = nullptr;
     auto count = [&]() -> int {
         BSM_TRY(tmp.get(&b_groups, std::max(1, B.nbrows)));
         return count_entries(A, B, b_groups, d_entries, s);
     };
     if (st == BSM_OK && may_group &&
-        (sizes || static_cast<double>(A.nnzb) * static_cast<double>(B.nnzb) >= 0.5 * least_products * A.nbcols))
+        (sizes || ((!own || fp64_least_reuse(A.uni_r) < 64.0) &&
+                   static_cast<double>(A.nnzb) * static_cast<double>(B.nnzb) >= 0.5 * least_products * A.nbcols)))
         st = count();
-    if (st == BSM_OK) st = sym_count(sa, c_row_ptr, c_nval, p_row_ptr, flops_row, s);
-    if (st == BSM_OK) st = scan_i64(c_row_ptr, c_row_ptr, nbr, s);
-    if (st == BSM_OK) st = scan_i64(c_nval, c_nval, nbr, s);
-    if (st == BSM_OK) st = scan_i64(p_row_ptr, p_row_ptr, nbr, s);
-    std::vector<int64_t> h_crp(ns), h_sums(3 * ns + 1);
+    std::vector<int64_t> h_crp(ns), h_sums(3 * ns + parts);
     if (st == BSM_OK) {
         hipError_t e = hipMemcpyAsync(h_crp.data(), c_row_ptr, sizeof(int64_t) * ns, hipMemcpyDeviceToHost, s);
-        if (e == hipSuccess) e = hipMemcpyAsync(h_sums.data(), sums, sizeof(int64_t) * (3 * ns + 1), hipMemcpyDeviceToHost, s);
+        if (e == hipSuccess) e = hipMemcpyAsync(h_sums.data(), sums, sizeof(int64_t) * (3 * ns + (b_groups ? parts : 0)), hipMemcpyDeviceToHost, s);
         if (e == hipSuccess) e = hipStreamSynchronize(s);
         if (e != hipSuccess) { set_error("multiply: reading sizes failed: %s", hipGetErrorString(e)); st = BSM_EDEVICE; }
     }
-    if (st == BSM_OK && may_group && !b_groups && static_cast<double>(h_sums[2 * ns - 1]) >= least_products) {
+    if (st == BSM_OK && may_group && !b_groups && static_cast<double>(h_sums[2 * ns - 1]) >= least_products &&
+        (!own || static_cast<double>(h_sums[2 * ns - 1]) >=
+                     fp64_least_reuse(A.uni_r) * static_cast<double>(h_crp[nbr]))) {
         st = count();
         hipError_t e = hipSuccess;
-        if (st == BSM_OK) e = hipMemcpyAsync(&h_sums[3 * ns], d_entries, sizeof(int64_t), hipMemcpyDeviceToHost, s);
+        if (st == BSM_OK) e = hipMemcpyAsync(&h_sums[3 * ns], d_entries, sizeof(int64_t) * parts, hipMemcpyDeviceToHost, s);
         if (st == BSM_OK && e == hipSuccess) e = hipStreamSynchronize(s);
         if (e != hipSuccess) { set_error("multiply: counting entries failed: %s", hipGetErrorString(e)); st = BSM_EDEVICE; }
     }
@@ -404,13 +411,14 @@ int multiply(double alpha, Mat &A, Mat &B, double beta, Mat &C, double eps, int 
     // the tuning table picks another kernel family for them
     const double reuse = nnzb_c ? static_cast<double>(nprod) / static_cast<double>(nnzb_c) : 0.0;
     // products per entry of 4 x 4 groups (unknown: large), and a bound of the groups
-    const double share = b_groups && h_sums[3 * ns] > 0
-                             ? static_cast<double>(nprod) / static_cast<double>(h_sums[3 * ns]) : 1e300;
+    int64_t entries = 0;
+    for (int p = 0; b_groups && p < parts; ++p) entries += h_sums[3 * ns + p];
+    const double share = entries > 0 ? static_cast<double>(nprod) / static_cast<double>(entries) : 1e300;
     auto most_groups = [&]() {
         const int64_t ncg = (B.nbcols + 3) / 4;
         int64_t n = 0;
         for (int32_t i = 0; i < nbr; i += 4) n += std::min(ncg, h_crp[std::min(nbr, i + 4)] - h_crp[i]);
-        return static_cast<double>(use_c || !b_groups ? n : std::min(n, h_sums[3 * ns]));
+        return static_cast<double>(use_c || !b_groups ? n : std::min(n, entries));
     };
     bool use_quad = false;
     if (prec == BSM_FP64 && variant == kSmmF64Quad && A.uni_r && A.uni_c && B.uni_c &&

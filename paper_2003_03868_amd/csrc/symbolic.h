@@ -99,9 +99,10 @@ struct MixedPairs {
 };
 void mixed_pairs(const std::vector<int32_t> &rbs, const std::vector<int32_t> &cbs, MixedPairs *mp);
 
-// *entries (device): how many entries the 4 x 4 groups of consecutive rows and
-// columns of C = A B have, from the patterns of A and B.  per_row: one word per
-// block row of B.  No wait.
+// How many entries the 4 x 4 groups of consecutive rows and columns of C = A B
+// have, from the patterns of A and B, as count_entries_parts(A) sums in device
+// memory.  per_row: one word per block row of B.  No wait.
+int count_entries_parts(const Mat &A);
 int count_entries(const Mat &A, const Mat &B, int32_t *per_row, int64_t *entries, hipStream_t s);
 // Workgroups of 256 threads that one launch of the list builders may have.
 constexpr int64_t kQuadListGroups = (int64_t{1} << 32) / 256 - 1;
