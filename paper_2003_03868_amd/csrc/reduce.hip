@@ -137,7 +137,8 @@ __global__ void k_compact_rows(const int64_t *row_ptr, const int64_t *kidx, int3
 // blocks; for small ones launching a workgroup per stored block was: 1.2
 // million blocks of 36 doubles took 297 us, with RUN 1 / 2 / 4 / 16 / 32 377 /
 // 261 / 200 / 154 / 150.  Mixed blocks of 280 doubles on average (4 GB kept)
-// 2049 us, now 2115 / 2020 / 2091 / 2203 / 2250.
+// 2049 us, now 2115 / 2020 / 2091 / 2203 / 2250.  Of few blocks a wave takes two
+// (a filter of 404 blocks of 11 x 11 62 us, with 16 of them 69).
 template <int RUN>
 __global__ void __launch_bounds__(256)
 k_compact_blocks(const int64_t *kidx, const int64_t *koff, const int32_t *col_idx,
@@ -207,7 +208,7 @@ int compact_by_norm(Mat &m, const double *sq, const double *mx, double eps, int 
         if (st == BSM_OK) {
             k_compact_rows<<<grid_for(m.nbrows + 1, 256), 256, 0, s>>>(m.row_ptr, kidx, m.nbrows,
                                                                       nm.row_ptr);
-            if (m.nvalues < 128 * n)
+            if (m.nvalues < 128 * n && n >= 16384)
                 k_compact_blocks<16><<<grid_for(n, 4 * 16), 256, 0, s>>>(
                     kidx, koff, m.col_idx, m.blk_off, m.values, n, nm.col_idx, nm.blk_off, nm.values);
             else

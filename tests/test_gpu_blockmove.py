@@ -75,3 +75,23 @@ def test_transpose_of_any_row_length(nbr, nbc, long_rows):
     o = np.lexsort((r, c))
     assert np.array_equal(got_ptr, ptr(c, nbc)) and np.array_equal(got_col, r[o])
     assert np.array_equal(got_val, val[o])
+
+
+@pytest.mark.parametrize("nblk", [8191, 8192, 8193, 9001])
+@pytest.mark.parametrize("size", [1, 6])
+def test_filter_of_many_small_blocks(nblk, size):
+    """Around the number of blocks from which a wave takes sixteen of them."""
+    from paper_2003_03868_amd import bsm
+    rng = np.random.default_rng(nblk + size)
+    a = synth.random_bsr(2, nblk, np.full(2, size), np.full(nblk, size), 1.0, rng)
+    keep = rng.random(a.nnzb) < 0.5
+    keep[:64] = False
+    keep[-64:] = True
+    blocks = a.values.reshape(a.nnzb, -1)
+    blocks[~keep] *= 1e-9
+    blocks[keep] += np.where(blocks[keep] < 0, -1.0, 1.0)
+    d = to_dev(a)
+    bsm.bsm_filter(d.handle, 1e-3)
+    got = from_dev(d)
+    assert np.array_equal(got.col_idx, a.col_idx[keep])
+    assert np.array_equal(got.values, blocks[keep].ravel())
