@@ -253,13 +253,13 @@ __global__ void k_sub_resid(const double *partial, const int32_t *act_sub, const
     r[a] = sqrt(s) / static_cast<double>(ndim[act_sub[a]]);
 }
 
-// Row sums of |H - mu I| of every stored block, one per row: those of block
-// row i follow sums[soff[i]], block after block.  One workgroup per block row
-// at a time, a thread per row of a block.
+// Row sums of |H - mu I| of every stored block, one per row: those of block t
+// at sums[t max_b].  One workgroup per block row at a time, a thread per row of
+// a block.
 __global__ __launch_bounds__(256) void k_sub_block_sums(const int64_t *row_ptr, const int32_t *col_idx,
                                                         const int64_t *blk_off, const double *vals,
                                                         const int32_t *rbs, int32_t nb, double mu,
-                                                        const int64_t *soff, double *sums) {
+                                                        int max_b, double *sums) {
     for (int i = blockIdx.x; i < nb; i += gridDim.x) {
         const int bi = rbs[i];
         const int64_t t0 = row_ptr[i], n = (row_ptr[i + 1] - t0) * bi;
@@ -269,7 +269,7 @@ __global__ __launch_bounds__(256) void k_sub_block_sums(const int64_t *row_ptr, 
             const double *h = vals + blk_off[t] + static_cast<int64_t>(u) * bj;
             double s = 0.0;
             for (int v = 0; v < bj; ++v) s += fabs(h[v] - ((j == i && u == v) ? mu : 0.0));
-            sums[soff[i] + q] = s;
+            sums[t * max_b + u] = s;
         }
     }
 }
@@ -290,7 +290,7 @@ __device__ inline int64_t sub_find(const int32_t *col_idx, int64_t p0, int64_t p
 // Reading the assembled T_j instead took 0.51 ms for 1.9 GB, and scaling it
 // afterwards 0.81 ms; this way the gather writes scaled values (MI355X, 6192
 // submatrices of mean edge 189).
-__global__ void k_sub_norm(const int64_t *row_ptr, const int32_t *col_idx, const int64_t *soff,
+__global__ void k_sub_norm(const int64_t *row_ptr, const int32_t *col_idx, int max_b,
                            const double *sums, const int32_t *rbs, const int32_t *ent_row,
                            const int32_t *ent_sub, const int64_t *sub_ent0, double *scale,
                            int64_t nent) {
@@ -302,7 +302,7 @@ __global__ void k_sub_norm(const int64_t *row_ptr, const int32_t *col_idx, const
     double row = 0.0;
     for (int64_t f0 = sub_ent0[sub]; f0 < f1; f0 += 64) {
         const int64_t t = f0 + lane < f1 ? sub_find(col_idx, p0, p1, ent_row[f0 + lane]) : p1;
-        const double *b = t < p1 ? sums + soff[i] + (t - p0) * bi : nullptr;
+        const double *b = t < p1 ? sums + t * max_b : nullptr;
         for (int u = 0; u < bi; ++u) {
             double s = b ? b[u] : 0.0;
 #pragma unroll
@@ -421,23 +421,7 @@ int submatrix_density(Mat &H, double mu, const bsm_sign_opts &o, Mat **p_out, bs
     BSM_HIP(hipMemcpyAsync(rp.data(), H.row_ptr, sizeof(int64_t) * (nb + 1), hipMemcpyDeviceToHost, s));
     if (H.nnzb)
         BSM_HIP(hipMemcpyAsync(ci.data(), H.col_idx, sizeof(int32_t) * H.nnzb, hipMemcpyDeviceToHost, s));
-    // whether H is its own transpose: half of every product is then the
-    // mirror image of the other
-    unsigned long long mirrored = 0;
-    const std::vector<unsigned long long> none(1, 0);
-    if (nb > 0) {
-        unsigned long long *d_mirrored = nullptr;
-        BSM_TRY(upload(&d_mirrored, none, s));
-        hipLaunchKernelGGL(k_sub_symmetric, dim3(std::min(nb, kRowGroups)), dim3(256), 0, s, H.row_ptr,
-                           H.col_idx, H.blk_off, H.values, H.rbs, nb, d_mirrored);
-        hipError_t e = hipGetLastError();
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(&mirrored, d_mirrored, sizeof(mirrored), hipMemcpyDeviceToHost, s);
-        dfree(d_mirrored, s);
-        BSM_HIP(e);
-    }
     BSM_HIP(hipStreamSynchronize(s));
-    const bool symmetric = mirrored == static_cast<unsigned long long>(H.nnzb);
     std::vector<int64_t> cp(nb + 1, 0);
     for (int64_t t = 0; t < H.nnzb; ++t) cp[ci[t] + 1]++;
     for (int j = 0; j < nb; ++j) cp[j + 1] += cp[j];
@@ -483,18 +467,17 @@ int submatrix_density(Mat &H, double mu, const bsm_sign_opts &o, Mat **p_out, bs
     }
     st->mean_dim = nb ? sum_dim / nb : 0.0;
 
-    const auto gemm = symmetric ? k_sub_gemm<true> : k_sub_gemm<false>;
+    // whether H is its own transpose, read back with the first batch's norms:
+    // half of every product is then the mirror image of the other
+    bool symmetric = false;
+    auto gemm = k_sub_gemm<false>;
     const size_t cap = batch_bytes_cap();
     std::vector<std::pair<hipEvent_t, hipEvent_t>> gev;
     double *d_sums = nullptr;        // row sums of |H - mu I| per block
-    int64_t *d_soff = nullptr;       // where those of a block row start
-    std::vector<int64_t> soff(nb + 1, 0);
-    for (int i = 0; i < nb; ++i) soff[i + 1] = soff[i] + (rp[i + 1] - rp[i]) * H.h_rbs[i];
-    if (rc == BSM_OK) rc = upload(&d_soff, soff, s);
-    if (rc == BSM_OK) rc = dalloc(&d_sums, std::max<int64_t>(soff[nb], 1), s);
+    if (rc == BSM_OK) rc = dalloc(&d_sums, std::max<int64_t>(H.nnzb * H.max_rbs, 1), s);
     if (rc == BSM_OK && nb > 0) {
         hipLaunchKernelGGL(k_sub_block_sums, dim3(std::min(nb, kRowGroups)), dim3(256), 0, s, H.row_ptr,
-                           H.col_idx, H.blk_off, H.values, H.rbs, nb, mu, d_soff, d_sums);
+                           H.col_idx, H.blk_off, H.values, H.rbs, nb, mu, H.max_rbs, d_sums);
         if (hipGetLastError() != hipSuccess) { set_error("submatrix: row sums failed"); rc = BSM_EDEVICE; }
     }
     int64_t n_noconv = 0;            // submatrices left above tol (every batch still runs)
@@ -558,14 +541,14 @@ int submatrix_density(Mat &H, double mu, const bsm_sign_opts &o, Mat **p_out, bs
         if (rc == BSM_OK) rc = dalloc(&buf0, static_cast<size_t>(tot), s);
         if (rc == BSM_OK) rc = dalloc(&buf1, static_cast<size_t>(tot), s);
         if (rc == BSM_OK) rc = dalloc(&ybuf, static_cast<size_t>(tot), s);
-        if (rc == BSM_OK) rc = dalloc(&d_scale, static_cast<size_t>(ns), s);
+        if (rc == BSM_OK) rc = dalloc(&d_scale, static_cast<size_t>(ns) + 1, s);
         if (rc == BSM_OK) rc = dalloc(&d_r, static_cast<size_t>(ns), s);
         if (rc != BSM_OK) { release(); break; }
 
         // X_0 = (T - mu I) / ||T - mu I||_inf, zero padding
         // (the products write the whole padded squares of the other buffers)
         if (hipMemsetAsync(buf0, 0, sizeof(double) * tot, s) != hipSuccess ||
-            hipMemsetAsync(d_scale, 0, sizeof(double) * ns, s) != hipSuccess) {
+            hipMemsetAsync(d_scale, 0, sizeof(double) * (ns + 1), s) != hipSuccess) {
             set_error("submatrix: memset failed");
             rc = BSM_EDEVICE;
             release();
@@ -573,16 +556,28 @@ int submatrix_density(Mat &H, double mu, const bsm_sign_opts &o, Mat **p_out, bs
         }
         if (nent > 0)
             hipLaunchKernelGGL(k_sub_norm, dim3(static_cast<unsigned>(nent)), dim3(64), 0, s,
-                               H.row_ptr, H.col_idx, d_soff, d_sums, H.rbs, d_erow, d_esub,
+                               H.row_ptr, H.col_idx, H.max_rbs, d_sums, H.rbs, d_erow, d_esub,
                                d_ent0, d_scale, nent);
-        std::vector<double> scale(ns);
-        if (hipMemcpyAsync(scale.data(), d_scale, sizeof(double) * ns, hipMemcpyDeviceToHost, s) !=
-                hipSuccess ||
-            hipStreamSynchronize(s) != hipSuccess) {
-            set_error("submatrix: %s", hipGetErrorString(hipGetLastError()));
+        if (j0 == 0)                 // into the word behind the norms
+            hipLaunchKernelGGL(k_sub_symmetric, dim3(std::min(nb, kRowGroups)), dim3(256), 0, s, H.row_ptr,
+                               H.col_idx, H.blk_off, H.values, H.rbs, nb,
+                               reinterpret_cast<unsigned long long *>(d_scale + ns));
+        std::vector<double> scale(ns + 1);
+        hipError_t e = hipGetLastError();
+        if (e == hipSuccess)
+            e = hipMemcpyAsync(scale.data(), d_scale, sizeof(double) * (ns + 1), hipMemcpyDeviceToHost, s);
+        if (e == hipSuccess) e = hipStreamSynchronize(s);
+        if (e != hipSuccess) {
+            set_error("submatrix: %s", hipGetErrorString(e));
             rc = BSM_EDEVICE;
             release();
             break;
+        }
+        if (j0 == 0) {
+            unsigned long long mirrored;
+            std::memcpy(&mirrored, &scale[ns], sizeof mirrored);
+            symmetric = mirrored == static_cast<unsigned long long>(H.nnzb);
+            if (symmetric) gemm = k_sub_gemm<true>;
         }
         for (int q = 0; q < ns && rc == BSM_OK; ++q) {
             if (!std::isfinite(scale[q])) {
@@ -730,7 +725,6 @@ int submatrix_density(Mat &H, double mu, const bsm_sign_opts &o, Mat **p_out, bs
         j0 = j1;
     }
     dfree(d_sums, s);
-    dfree(d_soff, s);
     if (rc == BSM_OK) {
         const int r2 = filter_inplace(*P, o.eps_filter, o.norm, s);
         if (r2 != BSM_OK) rc = r2;
