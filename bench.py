@@ -81,7 +81,7 @@ def cpu_baseline(h, rows: int, step_flops: float = 0.0, rows_1t: int = 96):
     return out
 
 
-KERNEL_SOURCES = ["smm.h", "smm_quad.hip", "smm_tile.hip", "lds_dma.h", "quad.hip", "multiply.hip", "graph_iter.hip"]
+KERNEL_SOURCES = ["smm.h", "smm_group.h", "smm_quad.hip", "smm_tile.hip", "lds_dma.h", "quad.hip", "multiply.hip", "graph_iter.hip"]
 
 
 def sources_sha256() -> str:

@@ -19,8 +19,8 @@
 // block rows, 14.7 products per C block 18.5 (persistent one-block kernel)
 // and 7.9 ms, 126 products 250 and 69 ms; sizes {5, 13, 23, 26}, 126 products
 // 95.7 (one launch per class) and 73.1 ms.  It is bound by the wait for LDS in
-// the step of a product (steps of 16 instructions at most between waits, two
-// waves per SIMD) and, with few entries per group, by the chain of loads that
+// the step of a product (steps of 16 instructions at most between waits, four
+// waves per SIMD: two groups share a CU's LDS) and, with few entries per group, by the chain of loads that
 // starts a group.  Tried: sixteen waves of one C block, one group per CU and
 // twice the stage: 11 .. 8% slower.
 #include "lds_dma.h"
