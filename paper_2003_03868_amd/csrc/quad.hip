@@ -358,8 +358,9 @@ k_row_col_groups(const int64_t *row_ptr, const int32_t *col_idx, int32_t nrows, 
 }
 
 // One workgroup per row group at a time; a bitmap in LDS tells the first block
-// of the four rows in a column.  A sum per workgroup: adding 1548 of them to one
-// word in memory took 18 us.
+// of the four rows in a column.  Where the columns need several passes over the
+// bitmap, the columns of few blocks are compared with each other instead.  A sum
+// per workgroup: adding 1548 of them to one word in memory took 18 us.
 constexpr int32_t kEntryWindow = 1 << 16;   // block columns of A per pass
 __global__ void __launch_bounds__(kQuadThreads)
 k_count_entries(const int64_t *row_ptr, const int32_t *col_idx, int32_t nrows, int32_t ncols,
@@ -370,6 +371,17 @@ k_count_entries(const int64_t *row_ptr, const int32_t *col_idx, int32_t nrows, i
     int64_t n = 0;
     for (int32_t g = blockIdx.x; g < ngroups; g += gridDim.x) {
         const int64_t b = row_ptr[4 * g], e = row_ptr[min(4 * g + 4, nrows)];
+        if (ncols > kEntryWindow && e - b <= kQuadThreads) {
+            const int t = threadIdx.x;
+            const uint32_t k = b + t < e ? col_idx[b + t] : 0u;
+            __syncthreads();
+            bits[t] = k;
+            __syncthreads();
+            bool first = b + t < e;
+            for (int u = 0; u < t && first; ++u) first = bits[u] != k;
+            if (first) n += col_groups[k];
+            continue;
+        }
         for (int64_t k0 = 0; k0 < ncols; k0 += kEntryWindow) {
             const int words = static_cast<int>(min(static_cast<int64_t>(kEntryWindow), ncols - k0) + 31) / 32;
             __syncthreads();

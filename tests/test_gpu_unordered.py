@@ -38,6 +38,10 @@ def _band(n, w, sizes, perm, rng):
     (0, (4,), 1500, 33, "k_smm_f64_tile", ("BSM_QUAD_MIN_REUSE", "0", "1e9")),
     (0, (9,), 1300, 33, "k_smm_f64_tile", ("BSM_QUAD_MIN_REUSE", "0", "1e9")),
     (0, (31,), 800, 33, "k_smm_f64_tile", ("BSM_QUAD_MIN_REUSE", "0", "1e9")),
+    # more block columns than a pass over the bitmap that counts entries has,
+    # with at most and more than 256 blocks per row group
+    (0, (4,), 66000, 33, "k_smm_f64_tile", ("BSM_QUAD_MIN_REUSE", "0", "1e9")),
+    (0, (4,), 66000, 65, "k_smm_f64_tile", ("BSM_QUAD_MIN_REUSE", "0", "1e9")),
     (0, OTHER, 2000, 9, "k_smm_f64_mtile", ("BSM_MIXED_TILE", "1", "0")),
     (0, BASIS, 1000, 9, "k_smm_f64_mtile", ("BSM_MIXED_TILE", "1", "0")),
     (0, BASIS, 900, 151, "k_smm_f64_mtile", ("BSM_MIXED_TILE", "1", "0")),
