@@ -140,12 +140,13 @@ static bool mixed_groups(bool basis, double reuse, double share, double nprod, d
 // Small blocks with few products per C block gain from the groups' shorter
 // stacks all the same where the groups are full (`full`; 2.3 products per C
 // block, share 1.1: three parts 5 0.54, 13 0.73, two parts 0.82, 0.98).
+static double fp32_least_reuse(int m) { return m == 32 ? 0.0 : m <= 13 ? 14.0 : 32.0; }
 static bool lowp_groups(int prec, int m, double reuse, double share, bool full, int64_t nprod) {
     const char *e = getenv("BSM_LOWP_QUAD");
     if (e) return atoi(e) != 0;
     const bool many = nprod >= 400000;
     if (prec == BSM_FP32)
-        return many && (m == 32 || reuse >= (m <= 13 ? 14.0 : 32.0)) &&
+        return many && reuse >= fp32_least_reuse(m) &&
                share >= (m == 32 ? 2.6 : m <= 13 ? 4.0 : 6.0);
     if (!many && static_cast<double>(nprod) * m < 4e6) return false;
     if (m <= 13 && reuse < 4.0 && full) return true;
@@ -299,25 +300,27 @@ int multiply(double alpha, Mat &A, Mat &B, double beta, Mat &C, double eps, int 
     if (st == BSM_OK) st = scan_i64(c_nval, c_nval, nbr, s);
     if (st == BSM_OK) st = scan_i64(p_row_ptr, p_row_ptr, nbr, s);
     // the entries that 4 x 4 groups would have, where a rule below looks at them:
-    // counted along with the rest (8 us) where as many products are to be
-    // expected, by themselves for the sizes that seldom have enough per C block
+    // counted along with the rest (8 us, 30 on a whole multiply) where as many
+    // products are to be expected; by themselves for sizes that seldom have
+    // enough of them per C block, and for mixed sizes that need them to decide
     const int variant = smm_variant();
     const bool mixed_sizes = !(A.uni_r && A.uni_c && B.uni_c);
     const bool square = A.uni_r && A.uni_r == A.uni_c && A.uni_r == B.uni_c;
-    const bool may_group = variant == kSmmF64Quad && tau == 0.0 && !getenv("BSM_SMM_VARIANT") &&
+    const bool may_group = variant == kSmmF64Quad && tau == 0.0 && square && !getenv("BSM_SMM_VARIANT") &&
                            !getenv("BSM_QUAD_MIN_REUSE") &&
-                           (prec == BSM_FP64 ? mixed_sizes || (square && smm_tile_available(A.uni_r))
-                                             : square && smm_lowp_available(A.uni_r, A.uni_r, A.uni_r));
+                           (prec == BSM_FP64 ? smm_tile_available(A.uni_r)
+                                             : smm_lowp_available(A.uni_r, A.uni_r, A.uni_r));
     const bool own = prec == BSM_FP64 && square && smm_quad_available(A.uni_r, A.uni_r, A.uni_r);
+    const double least_reuse = own ? fp64_least_reuse(A.uni_r) : prec == BSM_FP32 ? fp32_least_reuse(A.uni_r) : 0.0;
     const double least_products =                               // below, no rule looks at them
-        mixed_sizes ? 1000.0 : own ? 1e6 : prec == BSM_FP32 ? 4e5 : std::min(4e5, 4e6 / std::max(1, A.uni_r));
+        own ? 1e6 : prec == BSM_FP32 ? 4e5 : std::min(4e5, 4e6 / std::max(1, A.uni_r));
     int32_t *b_groups = nullptr;
     auto count = [&]() -> int {
         BSM_TRY(tmp.get(&b_groups, std::max(1, B.nbrows)));
         return count_entries(A, B, b_groups, d_entries, s);
     };
     if (st == BSM_OK && may_group &&
-        (sizes || ((!own || fp64_least_reuse(A.uni_r) < 64.0) &&
+        (sizes || (least_reuse <= 20.0 &&
                    static_cast<double>(A.nnzb) * static_cast<double>(B.nnzb) >= 0.5 * least_products * A.nbcols)))
         st = count();
     std::vector<int64_t> h_crp(ns), h_sums(3 * ns + parts);
@@ -327,15 +330,20 @@ int multiply(double alpha, Mat &A, Mat &B, double beta, Mat &C, double eps, int 
         if (e == hipSuccess) e = hipStreamSynchronize(s);
         if (e != hipSuccess) { set_error("multiply: reading sizes failed: %s", hipGetErrorString(e)); st = BSM_EDEVICE; }
     }
+    auto sum_entries_of = [&]() {
+        int64_t n = 0;
+        for (int p = 0; b_groups && p < parts; ++p) n += h_sums[3 * ns + p];
+        return n;
+    };
+    auto count_now = [&]() -> int {
+        BSM_TRY(count());
+        BSM_HIP(hipMemcpyAsync(&h_sums[3 * ns], d_entries, sizeof(int64_t) * parts, hipMemcpyDeviceToHost, s));
+        BSM_HIP(hipStreamSynchronize(s));
+        return BSM_OK;
+    };
     if (st == BSM_OK && may_group && !b_groups && static_cast<double>(h_sums[2 * ns - 1]) >= least_products &&
-        (!own || static_cast<double>(h_sums[2 * ns - 1]) >=
-                     fp64_least_reuse(A.uni_r) * static_cast<double>(h_crp[nbr]))) {
-        st = count();
-        hipError_t e = hipSuccess;
-        if (st == BSM_OK) e = hipMemcpyAsync(&h_sums[3 * ns], d_entries, sizeof(int64_t) * parts, hipMemcpyDeviceToHost, s);
-        if (st == BSM_OK && e == hipSuccess) e = hipStreamSynchronize(s);
-        if (e != hipSuccess) { set_error("multiply: counting entries failed: %s", hipGetErrorString(e)); st = BSM_EDEVICE; }
-    }
+        static_cast<double>(h_sums[2 * ns - 1]) >= least_reuse * static_cast<double>(h_crp[nbr]))
+        st = count_now();
     if (st != BSM_OK) { dfree(c_row_ptr, s); return st; }
     const int64_t nnzb_c = h_crp[nbr];
     const int64_t *h_prp = h_sums.data() + ns;
@@ -411,14 +419,13 @@ int multiply(double alpha, Mat &A, Mat &B, double beta, Mat &C, double eps, int 
     // the tuning table picks another kernel family for them
     const double reuse = nnzb_c ? static_cast<double>(nprod) / static_cast<double>(nnzb_c) : 0.0;
     // products per entry of 4 x 4 groups (unknown: large), and a bound of the groups
-    int64_t entries = 0;
-    for (int p = 0; b_groups && p < parts; ++p) entries += h_sums[3 * ns + p];
+    const int64_t entries = sum_entries_of();
     const double share = entries > 0 ? static_cast<double>(nprod) / static_cast<double>(entries) : 1e300;
     auto most_groups = [&]() {
         const int64_t ncg = (B.nbcols + 3) / 4;
         int64_t n = 0;
         for (int32_t i = 0; i < nbr; i += 4) n += std::min(ncg, h_crp[std::min(nbr, i + 4)] - h_crp[i]);
-        return static_cast<double>(use_c || !b_groups ? n : std::min(n, entries));
+        return n;
     };
     bool use_quad = false;
     if (prec == BSM_FP64 && variant == kSmmF64Quad && A.uni_r && A.uni_c && B.uni_c &&
@@ -456,9 +463,19 @@ int multiply(double alpha, Mat &A, Mat &B, double beta, Mat &C, double eps, int 
             for (int32_t b : v) m |= 1u << b;
             return __builtin_popcount(m);
         };
-        use_mtile = mixed_groups(mixed_ok, reuse, share, static_cast<double>(nprod), static_cast<double>(nnzb_c),
-                                 most_groups(), 0.5 * flops / static_cast<double>(nprod),
-                                 mixed_ok ? distinct(A.h_rbs) * distinct(B.h_cbs) : 0);
+        // as if entries and groups were as few as they can be, as many, as they are
+        const double n_c = static_cast<double>(nnzb_c), p = static_cast<double>(nprod);
+        auto pays = [&](double sh, double groups) {
+            return mixed_groups(mixed_ok, reuse, sh, p, n_c, groups, 0.5 * flops / p,
+                                mixed_ok ? distinct(A.h_rbs) * distinct(B.h_cbs) : 0);
+        };
+        const int64_t most = most_groups();
+        use_mtile = pays(16.0, n_c / 16.0);
+        if (use_mtile && !pays(1.0, static_cast<double>(most)) && st == BSM_OK) {
+            st = count_now();
+            const int64_t e = sum_entries_of();
+            if (e > 0) use_mtile = pays(p / static_cast<double>(e), static_cast<double>(use_c ? most : std::min(most, e)));
+        }
         if (const char *e = getenv("BSM_MIXED_TILE")) use_mtile = atoi(e) != 0;
         for (int b = 0; mixed_ok && b < 16; ++b) {
             static const int sz[4] = {5, 13, 23, 26};
@@ -473,7 +490,8 @@ int multiply(double alpha, Mat &A, Mat &B, double beta, Mat &C, double eps, int 
     if (prec != BSM_FP64 && variant == kSmmF64Quad && A.uni_r && A.uni_c && B.uni_c &&
         smm_lowp_available(A.uni_r, B.uni_c, A.uni_c))
         use_quad = lowp_tile = lowp_groups(prec, A.uni_r, reuse, share,
-                                           static_cast<double>(nnzb_c) >= 8.0 * most_groups(), nprod);
+                                           nnzb_c >= 8 * std::min(most_groups(), use_c || !entries ? INT64_MAX : entries),
+                                           nprod);
     // group shape: quads, or other shapes on request (FP64 only); screening
     // runs through the quads' product masks
     int GR = 2, GC = 2;
