@@ -304,7 +304,9 @@ k_smm_f64_fixed(SmmArgs a) {
 // metadata in registers instead of LDS (which leaves room for more waves), no
 // clearing of the tail, and the paths of each k one after the other instead of
 // a switch that copied the accumulators, the sixteen classes took 20.9 ms
-// instead of 27.0 (26 x 26 3.58 and 2.77, 5 x 5 0.54 and 0.46).
+// instead of 27.0 (26 x 26 3.58 and 2.77, 5 x 5 0.54 and 0.46): 72 scalar
+// instructions and 39 branches per product, matrix cores 37% busy, and operands
+// at 5.8 TB/s, above a large copy's 4.5.
 constexpr int kClassKmax = 26;   // largest k of the class set {5, 13, 23, 26}
 
 // Load, staging and multiply of one product with k known at compile time (the
