@@ -234,8 +234,17 @@ static int check_shapes(const Mat &A, const Mat &B, const Mat &C) {
     return BSM_OK;
 }
 
-int multiply(double alpha, Mat &A, Mat &B, double beta, Mat &C, double eps, int norm, int prec,
-             bsm_mult_stats *stats, hipStream_t s, MulPlan **plan, double tau, MulSizes *sizes) {
+// Most bytes that one list of the group kernels or one operand's image may
+// take (BSM_GROUP_BYTES; no bound by default).
+static size_t group_bytes_cap() {
+    const char *e = getenv("BSM_GROUP_BYTES");
+    return e ? static_cast<size_t>(strtoull(e, nullptr, 10)) : SIZE_MAX;
+}
+
+// `groups`: in, whether a rule may choose groups of C blocks; out, whether one did.
+static int multiply_once(double alpha, Mat &A, Mat &B, double beta, Mat &C, double eps, int norm, int prec,
+                         bsm_mult_stats *stats, hipStream_t s, MulPlan **plan, double tau, MulSizes *sizes,
+                         bool *groups_io) {
     BSM_TRY(check_shapes(A, B, C));
     if (!(tau >= 0.0) || !std::isfinite(tau)) { set_error("eps_screen must be finite and >= 0"); return BSM_EINVAL; }
     if (tau > 0.0 && (prec != BSM_FP64 || plan)) {
@@ -492,6 +501,8 @@ int multiply(double alpha, Mat &A, Mat &B, double beta, Mat &C, double eps, int 
         use_quad = lowp_tile = lowp_groups(prec, A.uni_r, reuse, share,
                                            nnzb_c >= 8 * std::min(most_groups(), use_c || !entries ? INT64_MAX : entries),
                                            nprod);
+    if (!*groups_io) use_quad = use_mtile = lowp_tile = false;
+    *groups_io = use_quad;
     // group shape: quads, or other shapes on request (FP64 only); screening
     // runs through the quads' product masks
     int GR = 2, GC = 2;
@@ -584,6 +595,10 @@ int multiply(double alpha, Mat &A, Mat &B, double beta, Mat &C, double eps, int 
         auto words = [&](const Mat &m) {
             return size ? lowp_image_words(m.nnzb, size, prec) : lowp_words(m.nvalues, prec);
         };
+        if (size && sizeof(uint32_t) * std::max(words(A), words(B)) > group_bytes_cap()) {
+            set_error("operand images above BSM_GROUP_BYTES");
+            st = BSM_ENOMEM;
+        }
         if (st == BSM_OK) st = keep_buf(&apk, words(A));
         if (st == BSM_OK) st = pack_operand(A, size, prec, false, apk, s);
         if (&A != &B || size) {
@@ -617,7 +632,10 @@ int multiply(double alpha, Mat &A, Mat &B, double beta, Mat &C, double eps, int 
             // groups of this chunk's C blocks and their merged entry lists;
             // without a plan the buffers live for this chunk only
             Scratch ctmp(s);
-            auto qbuf = [&](auto **ptr, size_t n) -> int { return pl ? keep_buf(ptr, n) : ctmp.get(ptr, n); };
+            auto qbuf = [&](auto **ptr, size_t n) -> int {
+                if (n * sizeof(**ptr) > group_bytes_cap()) { set_error("group lists above BSM_GROUP_BYTES"); return BSM_ENOMEM; }
+                return pl ? keep_buf(ptr, n) : ctmp.get(ptr, n);
+            };
             int32_t g0 = 0;
             int64_t npairs = (static_cast<int64_t>(r1 - r0) + GR - 1) / GR;
             if (use_mquad) {
@@ -916,6 +934,23 @@ int multiply(double alpha, Mat &A, Mat &B, double beta, Mat &C, double eps, int 
     }
     if (pl) { *plan = pl; pl = nullptr; }
     return BSM_OK;
+}
+
+// The lists of groups take up to four times the memory of the stacks (32 bytes
+// an entry, 8 a product), and images of both operands more than one packed
+// copy: where they do not fit, the multiply is done over again, one C block per
+// wave (C is only replaced at its end).  Screening has its products in groups
+// only.
+int multiply(double alpha, Mat &A, Mat &B, double beta, Mat &C, double eps, int norm, int prec,
+             bsm_mult_stats *stats, hipStream_t s, MulPlan **plan, double tau, MulSizes *sizes) {
+    bool groups = true;
+    int st = multiply_once(alpha, A, B, beta, C, eps, norm, prec, stats, s, plan, tau, sizes, &groups);
+    if (st == BSM_ENOMEM && groups && tau == 0.0) {
+        clear_error();
+        groups = false;
+        st = multiply_once(alpha, A, B, beta, C, eps, norm, prec, stats, s, plan, tau, sizes, &groups);
+    }
+    return st;
 }
 
 }  // namespace bsm
